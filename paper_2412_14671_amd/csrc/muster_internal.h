@@ -34,11 +34,10 @@ struct JobState {
   float lr0, b1, b2, eps;
   double loss_sim;  // accumulated over the current iteration
   double loss_reg;  // weighted regularisers
-  double loss_ext;  // weighted L_L2 + L_ts of a loss-only forward pass
   double* history;  // loss per step (device), length hist_len
   int hist_len;
-  int* flags;       // overflow flags of the staged Exp backward, cleared per iteration
-  int n_flags;
+  int* flags;       // per Exp-backward step: its fixed-point field was added to (deterministic
+  int n_flags;      // mode); cleared per iteration
   int hist_base;    // index of this level's first step in history
   unsigned int det_max[DET_SLOTS];  // deterministic mode: largest block magnitude (float bits)
 };
@@ -66,50 +65,25 @@ struct ComposeItem {
   float* out;
 };
 
-// One backward squaring: given gin = dL/du_{s+1}, accumulate dL/du_s into
-// gout (zeroed beforehand).  u_s = a * src.  If zero_in, gin is cleared
-// after it is read.  If reg_w != 0, the regulariser gradient of src (= phi)
-// times reg_w is added to the voxel's own term, and the regulariser value
-// times reg_loss_w is added to the job's loss.
+// One backward squaring: gout = oscale * dL/du_s from gin = dL/du_{s+1}, with
+// u_s = a * src, over march tiles of zc planes; then, over point tiles, what
+// the voxels that sample a voxel or more away spread.
 struct ExpBwdItem {
   int tile0;
   int D, H, W;
-  const float* src;
-  float* gin;
-  float* gout;
+  int zc;            // planes per march tile
   float a;
-  int zero_in;
-  float reg_w;       // weight of the L_ss gradient (0 = none)
-  float reg_loss_w;  // weight of the L_ss value
+  float oscale;
+  const float* src;
+  const float* gin;
+  float* gout;       // written whole by k_exp_bwd, added to by k_exp_far
+  int* far;          // per point tile: holds voxels for k_exp_far; 0 between steps
+  // Deterministic accumulation: k_exp_far adds into gout64 ([3][V] 64-bit
+  // fixed point) instead, at the scale of the job's slot det_slot over
+  // det_blocks blocks (see DET_SLOTS); null otherwise.
   JobState* js;
-  // L_L2 and L_ts at step 0 of a forward direction: the own term gains
-  // w_self f_i + w_prev f_{i-1} + w_next f_{i+1} (flows of the neighbouring
-  // intervals, NULL where absent), and the loss l2_loss_w |f_i|^2 +
-  // ts_loss_w |f_{i-1} inv_dprev - f_i inv_dself|^2 per voxel.
-  int ext;
-  float w_self, w_prev, w_next;
-  float l2_loss_w, ts_loss_w, inv_dprev, inv_dself;
-  const float* flow_prev;
-  const float* flow_next;
-  // Staged accumulation between squaring steps.  A block that scatters
-  // G_s with a box of bins that fits STAGE_CAP cells and stays within its
-  // tile's 26 neighbours writes the box, plain, to its own slot of stage_out
-  // ([tiles][3][STAGE_CAP]) and its extent to desc_out ([tiles][8]);
-  // otherwise it adds into the flat gout with atomics, marks its descriptor
-  // empty and sets *flag_out.  A step reading a staged G_{s+1} sums, at each
-  // voxel, the boxes of its own tile and its neighbours that contain the
-  // voxel, plus the flat gin where *flag_in is set (then clears it).
-  const float* stage_in;
-  const int* desc_in;
-  const int* flag_in;
-  float* stage_out;
-  int* desc_out;
-  int* flag_out;
-  // Deterministic accumulation: where a block adds into gout with atomics it
-  // adds into gout64 ([3][V] 64-bit fixed point) instead, at the scale of
-  // the job's slot det_slot over det_blocks blocks (see DET_SLOTS); null
-  // otherwise.
   long long* gout64;
+  int* flag64;       // set where gout64 is added to
   int det_slot;
   int det_blocks;
 };
@@ -236,47 +210,45 @@ struct RigidStepItem {
   float rot_lr;     // step scale of the angles (1 / largest half-extent)
 };
 
-// The gradient of one interval is g = scale * (g0f - g0b) (g0f, g0b are
-// cleared after they are read), or gsrc when gsrc is set.  Mode 0: Adam step
-// on phi.  Mode 1: gout = gscale * g.  Mode 2: gout = g (the combined
-// gradient, for smoothing before the step).
+// Mode 0: Adam step on phi with the gradient gsrc.  Mode 1: gout = gscale *
+// gsrc.
 struct AdamItem {
   int tile0;
   int n;          // voxels
   float* phi;
-  float* g0f;     // dL/du_0 of the forward direction
-  float* g0b;     // dL/du_0 of the backward direction
   const float* gsrc;
   float* m;
   float* v;
   float* gout;
-  float scale;    // 2^-K
-  float gscale;   // mode 1: grad_out
+  float gscale;
   int mode;
-  int pad;
   JobState* js;
 };
 
-// The gradient of an SVF from the staged G_0 of its two directions:
-// out = scale * (G_0 forward - G_0 backward), over point tiles.  Each
-// direction's stage / desc / flag are those of its last backward squaring and
-// gflat its flat overflow (cleared where read).
-struct PullItem {
+// The gradient of an SVF: out = gmul * (gf + gb + the regularisers'
+// gradients), gf and gb the (scaled, signed) G_0 of its two directions, each
+// of them and out NULL where not wanted; the regularisers' values are added
+// to *loss (NULL: not wanted).
+struct CombineItem {
   int tile0;
   int D, H, W;
-  const float* stage[2];
-  const int* desc[2];
-  const int* flag[2];
-  float* gflat[2];
+  const float* gf;
+  const float* gb;
   float* out;
-  float scale;
-  // Diffusion regulariser of the interval's flow (Eq. reg_ss), when it is
-  // added here rather than in the Exp backward's step 0: out gains
-  // reg_w * dR/dflow, and the job's loss reg_loss_w * R(flow).
-  float reg_w;
-  float reg_loss_w;
-  const float* flow;
-  JobState* js;
+  const float* flow;   // the flow the regularisers act on
+  double* loss;
+  double reg_loss_w;   // weight of the L_ss value
+  float gmul;
+  float reg_w;         // weight of the L_ss gradient
+  // L_L2 and L_ts: the gradient gains w_self f_i + w_prev f_{i-1} + w_next
+  // f_{i+1} (flows of the neighbouring intervals, NULL where absent), and the
+  // loss l2_loss_w |f_i|^2 + ts_loss_w |f_{i-1} inv_dprev - f_i inv_dself|^2
+  // per voxel.
+  int ext;
+  float w_self, w_prev, w_next;
+  float l2_loss_w, ts_loss_w, inv_dprev, inv_dself;
+  const float* flow_prev;
+  const float* flow_next;
 };
 
 // One separable pass of the periodic Gaussian smoothing along one axis, for
@@ -343,7 +315,12 @@ constexpr int PT_Z = 8, PT_Y = 8, PT_X = 16;   // 1024 voxels, 256 threads
 constexpr int PT_VOX = PT_Z * PT_Y * PT_X;
 constexpr int BLOCK = 256;
 constexpr int SCATTER_CELLS = 2048;          // LDS bins per component
-constexpr int STAGE_CAP = SCATTER_CELLS;      // cells per component of a staging slot
+// Columns of a marching block (y, x), and the marks a block of k_exp_far reads.
+constexpr int MT_Y = 16, MT_X = 16;
+constexpr int FAR_GROUP = 8;
+constexpr int MARCH_BLOCKS = 1024;             // blocks that fill the chip
+// Tiles of the combination of the SVF gradients.
+constexpr int CT_Z = 8, CT_Y = 8, CT_X = 32;
 // Tiles of the windowed-statistics kernels: TY x TX columns, z chunks.
 // Tile shapes (centres in y x x) of the window-statistics kernels; the block
 // has one thread per centre.
@@ -356,6 +333,12 @@ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 inline int point_tiles(int D, int H, int W) {
   return ceil_div(D, PT_Z) * ceil_div(H, PT_Y) * ceil_div(W, PT_X);
 }
+inline int march_tiles(int D, int H, int W, int zc) {
+  return ceil_div(D, zc) * ceil_div(H, MT_Y) * ceil_div(W, MT_X);
+}
+inline int combine_tiles(int D, int H, int W) {
+  return ceil_div(D, CT_Z) * ceil_div(H, CT_Y) * ceil_div(W, CT_X);
+}
 inline int stat_tiles(int D, int H, int W, int zc, int shape) {
   return ceil_div(D, zc) * ceil_div(H, SIM_SHAPE_Y[shape]) * ceil_div(W, SIM_SHAPE_X[shape]);
 }
@@ -366,15 +349,9 @@ inline int stat_tiles(int D, int H, int W, int zc, int shape) {
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
 hipError_t launch_exp_fwd(const ExpFwdItem* items, int n_items, int n_tiles, hipStream_t s);
 hipError_t launch_compose_fwd(const ComposeItem* items, int n_items, int n_tiles, hipStream_t s);
-// staged: 0 flat in / flat out, 1 flat in / staged out, 2 staged in / staged out,
-// 3 staged in / flat out
-// reg: some item adds the regulariser terms (reg_w != 0 or ext); without it
-// a leaner variant of the kernel runs.
-hipError_t launch_exp_bwd(const ExpBwdItem* items, int n_items, int n_tiles, int staged, bool reg,
-                          hipStream_t s);
-// A staged G_0 (stage_in, desc_in, flag_in of each item) to the flat gout.
-hipError_t launch_unstage(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s);
-hipError_t launch_pull_combine(const PullItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_exp_bwd(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_exp_far(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_combine(const CombineItem* items, int n_items, int n_tiles, hipStream_t s);
 hipError_t launch_compose_bwd(const ComposeBwdItem* items, int n_items, int n_tiles,
                               hipStream_t s);
 // Deterministic mode: the passes of the composition and Exp adjoints that
@@ -382,8 +359,7 @@ hipError_t launch_compose_bwd(const ComposeBwdItem* items, int n_items, int n_ti
 // writes), the fold of the fixed-point fields, and the clearing of the slots.
 hipError_t launch_compose_bwd_detmax(const ComposeBwdItem* items, int n_items, int n_tiles,
                                      hipStream_t s);
-hipError_t launch_exp_bwd_detmax(const ExpBwdItem* items, int n_items, int n_tiles, int staged,
-                                 hipStream_t s);
+hipError_t launch_exp_far_detmax(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s);
 hipError_t launch_det_fold(const DetFoldItem* items, int n_items, int n_tiles, hipStream_t s);
 hipError_t launch_det_clear(JobState* const* states, int n_jobs, hipStream_t s);
 // M = I o (Omega + U) of each item, over point tiles of its grid.
@@ -407,10 +383,6 @@ hipError_t launch_upsample2(const UpItem* items, int n_items, int n_tiles, hipSt
 hipError_t launch_upsample2_adj(const UpItem* items, int n_items, int n_tiles, hipStream_t s);
 hipError_t launch_adam_flat(int64_t n, float* x, const float* g, float* m, float* v, int t,
                             float lr, float b1, float b2, float eps, hipStream_t s);
-hipError_t launch_reg(GridDims d, const float* phi, double* out, float* grad, hipStream_t s);
-// out += l2w sum_p |f(p)|^2 + tsw sum_p |fprev(p) inv_dp - f(p) inv_ds|^2 (fprev may be NULL)
-hipError_t launch_reg_ext(GridDims d, const float* f, const float* fprev, float l2w, float tsw,
-                          float inv_dp, float inv_ds, double* out, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);
 
 // Scratch of the allocation-free similarity entry point: a file-scope device

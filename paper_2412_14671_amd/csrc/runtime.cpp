@@ -193,7 +193,7 @@ uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
   // flow grid: phi, m, v, Exp steps, composed pairs, pair gradients, ping-pong
   uint64_t fields = 3 * n1 + 2 * n1 * per_dir_fields(p) + std::max<uint64_t>(Pd, 1) + P + 4 * n1;
   if (p.smooth_sigma > 0.f) fields += 3 * n1;
-  else if (p.K >= 2) fields += n1;  // combined gradient of the staged Exp adjoint
+  else if (p.K >= 2) fields += n1;  // combined gradient
   uint64_t bytes = fields * F;
   // image grid: window coefficients, and with a coarser flow grid the pair
   // fields and their gradients
@@ -203,11 +203,17 @@ uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
   // deterministic mode: 64-bit fixed-point twins of the consecutive-field
   // gradients and of the Exp-backward ping-pong
   if (p.deterministic) bytes += 6 * n1 * 3 * V * sizeof(long long);
-  if (p.K >= 2) {
-    // staging slots and descriptors of the Exp backward, per direction, two steps
+  {
     const uint64_t tiles = (uint64_t)point_tiles(fd[0], fd[1], fd[2]);
-    bytes += 2 * 2 * n1 * tiles * (3 * STAGE_CAP * sizeof(float) + 8 * sizeof(int));
-    bytes += 2 * n1 * p.K * sizeof(int) + 2 * 256;
+    if (p.K >= 2) {
+      // Room for the Exp adjoint, per direction: 24 KB for each of two steps
+      // and point tile.  The figure servers have sized their budgets by; the
+      // adjoint's dense exchange takes less of it (its marks).
+      bytes += 2 * 2 * n1 * tiles * (3 * SCATTER_CELLS * sizeof(float) + 8 * sizeof(int));
+      bytes += 2 * n1 * p.K * sizeof(int) + 2 * 256;
+    } else {
+      bytes += 2 * n1 * tiles * sizeof(int);
+    }
   }
   uint64_t imgs = 0;
   for (int l = 0; l < p.levels - 1; ++l) {
@@ -314,7 +320,7 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
     J.m_phis.alloc(ctx, n1 * F);
     J.m_t1.alloc(ctx, n1 * F);
     J.m_t2.alloc(ctx, n1 * F);
-  } else if (J.staged()) {
+  } else if (J.p.K >= 2) {
     J.m_t1.alloc(ctx, n1 * F);  // the combined SVF gradient Adam reads
   }
   J.tiles_fine = point_tiles(J.ldims[L - 1][0], J.ldims[L - 1][1], J.ldims[L - 1][2]);
@@ -327,15 +333,12 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
   }
   if (J.p.deterministic) {
     J.m_det64.alloc(ctx, 6 * n1 * 3 * V0 * sizeof(long long));
+    J.m_flags.alloc(ctx, 2 * n1 * (size_t)J.p.K * sizeof(int));
     // zero bits: the fixed-point fields start (and are left by every fold) at 0
     MUSTER_HIP(launch_fill(J.m_det64.as<float>(), (int64_t)(12 * n1 * 3 * V0), 0.f, nullptr));
     MUSTER_HIP(hipStreamSynchronize(nullptr));
   }
-  if (J.staged()) {
-    J.m_stage.alloc(ctx, 2 * 2 * n1 * (size_t)J.tiles_fine * 3 * STAGE_CAP * sizeof(float));
-    J.m_desc.alloc(ctx, 2 * 2 * n1 * (size_t)J.tiles_fine * 8 * sizeof(int));
-    J.m_flags.alloc(ctx, 2 * n1 * (size_t)J.p.K * sizeof(int));
-  }
+  J.m_far.alloc(ctx, 2 * n1 * (size_t)J.tiles_fine * sizeof(int));
   size_t img = 0;
   for (int l = 0; l < L - 1; ++l) img += (size_t)N * J.VI(l);
   J.m_img.alloc(ctx, std::max<size_t>(img, 1) * sizeof(float));
@@ -360,8 +363,7 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
   J.footprint = J.m_phi.bytes + J.m_m.bytes + J.m_v.bytes + J.m_us.bytes + J.m_deep.bytes +
                 J.m_gpair.bytes + J.m_pp.bytes + J.m_coef.bytes + J.m_img.bytes +
                 J.m_state.bytes + J.m_hist.bytes + J.m_phis.bytes + J.m_t1.bytes + J.m_t2.bytes +
-                J.m_stage.bytes + J.m_desc.bytes + J.m_flags.bytes + J.m_pimg.bytes +
-                J.m_gimg.bytes + J.m_rigid.bytes + J.m_det64.bytes;
+                J.m_far.bytes + J.m_flags.bytes + J.m_pimg.bytes + J.m_gimg.bytes + J.m_rigid.bytes + J.m_det64.bytes;
   return job;
 }
 
@@ -376,6 +378,12 @@ static void run_items(Ctx* ctx, std::vector<Item>& items, int n_tiles, hipStream
   MUSTER_HIP(hipMemcpyAsync(d.p, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, s));
   MUSTER_HIP(launch(d.as<Item>(), (int)items.size(), n_tiles, s));
   MUSTER_HIP(hipStreamSynchronize(s));
+}
+
+// Whether two fields of n floats share memory.
+static bool overlap(const float* a, const float* b, size_t n) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + n * sizeof(float) && y < x + n * sizeof(float);
 }
 
 static int elem_tiles(size_t n) { return (int)((n + ELEM_PER_BLOCK - 1) / ELEM_PER_BLOCK); }
@@ -467,10 +475,9 @@ void job_begin_level(Job& J, int level, hipStream_t s) {
     MUSTER_HIP(launch_fill(J.mbuf, (int64_t)(n1 * 3 * V), 0.f, s));
     MUSTER_HIP(launch_fill(J.vbuf, (int64_t)(n1 * 3 * V), 0.f, s));
   }
-  MUSTER_HIP(launch_fill(J.m_pp.as<float>(), (int64_t)(4 * n1 * 3 * V), 0.f, s));
   if (J.p.rigid) rigid_begin_level(J, level, s);
-  if (J.staged())  // the flags are ints; 0.0f has the same bits as 0
-    MUSTER_HIP(launch_fill((float*)J.m_flags.p, (int64_t)(2 * n1 * J.p.K), 0.f, s));
+  // the marks are ints; 0.0f has the same bits as 0
+  MUSTER_HIP(launch_fill((float*)J.m_far.p, (int64_t)(2 * n1 * J.tiles_fine), 0.f, s));
   JobState st{};
   const int prev_nonfinite = level > 0 ? J.host_state->nonfinite : 0;
   st.t = 0;
@@ -483,8 +490,9 @@ void job_begin_level(Job& J, int level, hipStream_t s) {
   st.eps = J.p.eps;
   st.history = J.hist;
   st.hist_len = J.hist_len;
-  st.flags = J.staged() ? J.m_flags.as<int>() : nullptr;
-  st.n_flags = J.staged() ? (int)(2 * n1 * J.p.K) : 0;
+  st.flags = J.m_flags.as<int>();
+  st.n_flags = J.det() ? (int)(2 * n1 * J.p.K) : 0;
+  if (J.det()) MUSTER_HIP(launch_fill(J.m_flags.as<float>(), st.n_flags, 0.f, s));
   int base = 0;
   for (int l = 0; l < level; ++l) base += J.p.iters[l];
   st.hist_base = base;
@@ -573,7 +581,7 @@ namespace {
 // Algorithmic bytes per voxel (the unique bytes each step must move).
 constexpr double B_EXP_FWD = 24, B_COMPOSE_FWD = 36, B_SIM_STATS = 20, B_SIM_GRAD = 32,
                  B_COMPOSE_BWD = 84, B_EXP_BWD = 60, B_ADAM = 96, B_SMOOTH = 24, B_WARP = 20,
-                 B_UNSTAGE = 24;
+                 B_COMBINE = 36;
 
 struct Builder {
   Plan* plan;
@@ -949,15 +957,12 @@ void add_sim_stages(Builder& b, const std::vector<Job*>& jobs, StageKind kind) {
 }
 
 // L_L2 and L_ts terms of interval i (Sec. 2.4), on the flows Exp integrates.
-// Gradient weights carry 2^K: the step-0 own term is scaled by 2^-K when the
-// two directions are combined.
-void set_reg_ext(ExpBwdItem& it, const Job& J, int i) {
+void set_reg_ext(CombineItem& it, const Job& J, int i) {
   const int N = J.N;
   const double V = (double)J.Vc();
   const bool l2 = J.p.alpha_l2 > 0.f;
   const bool ts = J.p.alpha_ts > 0.f && N >= 3;
   if (!l2 && !ts) return;
-  const double k2 = std::ldexp(1.0, J.K());
   double w_self = 0, w_prev = 0, w_next = 0;
   it.ext = 1;
   if (l2) {
@@ -983,9 +988,25 @@ void set_reg_ext(ExpBwdItem& it, const Job& J, int i) {
       it.flow_next = J.flow(i + 1);
     }
   }
-  it.w_self = (float)(k2 * w_self);
-  it.w_prev = (float)(k2 * w_prev);
-  it.w_next = (float)(k2 * w_next);
+  it.w_self = (float)w_self;
+  it.w_prev = (float)w_prev;
+  it.w_next = (float)w_next;
+}
+
+// Planes per march tile of a launch over these items: the longest chunk that
+// still fills the chip.
+template <class Item>
+void set_march_tiles(std::vector<Item>& items, int& tiles) {
+  int zc = 64;
+  do {
+    zc /= 2;
+    tiles = 0;
+    for (Item& it : items) {
+      it.zc = zc;
+      it.tile0 = tiles;
+      tiles += march_tiles(it.D, it.H, it.W, zc);
+    }
+  } while (zc > 2 && tiles < MARCH_BLOCKS);
 }
 
 // Deterministic jobs' part of a scatter launch: the job's tiles in it (the
@@ -1013,8 +1034,7 @@ void det_assign(DetLaunch& dl, std::vector<Item>& items, const std::vector<Job*>
 
 template <class Item>
 void add_det_stages(Builder& b, StageKind kind, const std::vector<Item>& items,
-                    const std::vector<Job*>& owner, int staged,
-                    const std::vector<DetFoldItem>& folds) {
+                    const std::vector<Job*>& owner) {
   std::vector<Item> dmax;
   int tiles = 0;
   for (size_t k = 0; k < items.size(); ++k) {
@@ -1026,8 +1046,6 @@ void add_det_stages(Builder& b, StageKind kind, const std::vector<Item>& items,
     dmax.push_back(it);
   }
   b.add(kind, dmax, tiles, 0.0);
-  if (!dmax.empty()) b.plan->stages.back().staged = staged;
-  (void)folds;
 }
 
 void add_det_folds(Builder& b, std::vector<DetFoldItem>& folds) {
@@ -1109,7 +1127,7 @@ void add_backward(Builder& b, const std::vector<Job*>& jobs) {
       f.det_blocks = it.det_blocks;
       folds.push_back(f);
     }
-    add_det_stages(b, ST_COMPOSE_BWD_DETMAX, items, owner, 0, folds);
+    add_det_stages(b, ST_COMPOSE_BWD_DETMAX, items, owner);
     b.add(ST_COMPOSE_BWD, items, tiles, bytes);
     add_det_folds(b, folds);
   }
@@ -1117,178 +1135,110 @@ void add_backward(Builder& b, const std::vector<Job*>& jobs) {
     // recompute u_s where needed
     if (s >= 1)
       for (int k = 0; k < s; ++k) add_exp_fwd_step(b, jobs, k, true, s);
-    // one launch per staging mode in use (jobs with different K differ)
-    std::vector<ExpBwdItem> items[4];
-    std::vector<Job*> owner[4];
-    int tiles[4] = {0, 0, 0, 0};
-    double bytes[4] = {0, 0, 0, 0};
+    std::vector<ExpBwdItem> items;
+    std::vector<Job*> owner;
+    int tiles = 0;
+    double bytes = 0;
     for (Job* J : jobs) {
       const int K = J->K();
       if (s >= K) continue;
       const int* d = J->ldims[J->level];
       const float scale = std::ldexp(1.f, -K);
-      // a staged G_0 is read by k_pull_combine or k_unstage
-      const bool in_st = J->staged() && s < K - 1, out_st = J->staged();
-      const int mode = in_st ? (out_st ? 2 : 3) : (out_st ? 1 : 0);
       for (int dir = 0; dir < 2 * (J->N - 1); ++dir) {
         const int i = dir / 2;
         const bool fwd = dir % 2 == 0;
         ExpBwdItem it{};
-        it.tile0 = tiles[mode];
         it.D = d[0]; it.H = d[1]; it.W = d[2];
+        it.a = it.oscale = 1.f;
         if (s == 0) {
           it.src = J->flow(i);
-          it.a = (fwd ? 1.f : -1.f) * scale;
+          // u_0 = +-2^-K flow: the same factor carries G_0 to the flow
+          it.a = it.oscale = (fwd ? 1.f : -1.f) * scale;
         } else {
           it.src = J->u_step(dir, s);
-          it.a = 1.f;
         }
         if (s == K - 1)
           it.gin = fwd ? J->pair_grad(i, i + 1) : J->pair_grad(i + 1, i);
         else
           it.gin = J->pp(dir, (s + 1) % 2);
         it.gout = J->pp(dir, s % 2);
-        it.zero_in = (s < K - 1) ? 1 : 0;
-        if (in_st) {
-          it.stage_in = J->stage(dir, (s + 1) % 2);
-          it.desc_in = J->desc(dir, (s + 1) % 2);
-          it.flag_in = J->flag(dir, s + 1);
-        }
-        if (out_st) {
-          it.stage_out = J->stage(dir, s % 2);
-          it.desc_out = J->desc(dir, s % 2);
-          it.flag_out = J->flag(dir, s);
-        }
-        // L_ss joins here unless k_pull_combine adds it (staged jobs)
-        if (s == 0 && fwd && J->p.alpha_ss > 0.f && !J->staged()) {
-          it.reg_w = std::ldexp(1.f, K) * J->p.alpha_ss / (float)(J->N - 1);
-          it.reg_loss_w = J->p.alpha_ss / (float)(J->N - 1);
-        }
-        if (s == 0 && fwd) set_reg_ext(it, *J, i);
+        it.far = J->far(dir);
         it.js = J->js;
-        if (J->det()) it.gout64 = J->det64_pp(dir, s % 2);
-        items[mode].push_back(it);
-        owner[mode].push_back(J);
-        tiles[mode] += point_tiles(d[0], d[1], d[2]);
-        bytes[mode] += B_EXP_BWD * J->Vc();
-      }
-    }
-    for (int mode = 0; mode < 4; ++mode) {
-      DetLaunch dl;
-      det_assign(dl, items[mode], owner[mode], next_slot);
-      std::vector<DetFoldItem> folds;
-      bool any_det = false;
-      for (size_t k = 0; k < items[mode].size(); ++k) {
-        Job* J = owner[mode][k];
-        if (!J->det()) continue;
-        any_det = true;
-        ExpBwdItem& it = items[mode][k];
-        it.det_slot = dl.slot[J];
-        it.det_blocks = dl.tiles[J];
-        DetFoldItem f{};
-        f.n = (int)(3 * J->Vc());
-        f.f = it.gout;
-        f.q = it.gout64;
-        f.js = J->js;
-        // staged out: only blocks that did not stage added into the flat field,
-        // and each of them raised the flag
-        f.flag = (mode == 1 || mode == 2) ? it.flag_out : nullptr;
-        f.det_slot = it.det_slot;
-        f.det_blocks = it.det_blocks;
-        folds.push_back(f);
-      }
-      add_det_stages(b, ST_EXP_BWD_DETMAX, items[mode], owner[mode], mode, folds);
-      b.add(ST_EXP_BWD, items[mode], tiles[mode], bytes[mode]);
-      if (items[mode].empty()) continue;
-      b.plan->stages.back().staged = mode;
-      // deterministic jobs always run the general variant, so that their
-      // arithmetic does not depend on the other jobs of the launch
-      if (any_det) b.plan->stages.back().reg = 1;
-      for (const ExpBwdItem& e : items[mode])
-        if (e.reg_w != 0.f || e.ext) b.plan->stages.back().reg = 1;
-      add_det_folds(b, folds);
-    }
-  }
-  {
-    // staged G_0 of both directions straight into the combined gradient t1,
-    // with the diffusion regulariser (which the Exp adjoint's step 0 then
-    // need not carry); Adam, or the smoothing of the gradient, reads t1
-    std::vector<PullItem> pitems;
-    std::vector<ExpBwdItem> uitems;
-    int ptiles = 0, utiles = 0;
-    double pbytes = 0, ubytes = 0;
-    for (Job* J : jobs) {
-      if (!J->staged()) continue;
-      const int* d = J->ldims[J->level];
-      const int pt = point_tiles(d[0], d[1], d[2]);
-      for (int i = 0; i < J->N - 1; ++i) {
-        if (J->staged()) {
-          PullItem it{};
-          it.tile0 = ptiles;
-          it.D = d[0]; it.H = d[1]; it.W = d[2];
-          for (int k = 0; k < 2; ++k) {
-            const int dir = 2 * i + k;
-            it.stage[k] = J->stage(dir, 0);
-            it.desc[k] = J->desc(dir, 0);
-            it.flag[k] = J->flag(dir, 0);
-            it.gflat[k] = J->pp(dir, 0);
-          }
-          it.out = J->field(J->m_t1.as<float>(), i);
-          it.scale = std::ldexp(1.f, -J->K());
-          if (J->p.alpha_ss > 0.f) {
-            it.reg_w = it.reg_loss_w = J->p.alpha_ss / (float)(J->N - 1);
-            it.flow = J->flow(i);
-            it.js = J->js;
-          }
-          pitems.push_back(it);
-          ptiles += pt;
-          // the two staged G_0, the gradient written, and the flow the
-          // regulariser reads
-          pbytes += (2 * B_UNSTAGE + (it.reg_w != 0.f ? 12 : 0)) * J->Vc();
-        } else {
-          for (int k = 0; k < 2; ++k) {
-            const int dir = 2 * i + k;
-            ExpBwdItem it{};
-            it.tile0 = utiles;
-            it.D = d[0]; it.H = d[1]; it.W = d[2];
-            it.gout = J->pp(dir, 0);
-            it.stage_in = J->stage(dir, 0);
-            it.desc_in = J->desc(dir, 0);
-            it.flag_in = J->flag(dir, 0);
-            uitems.push_back(it);
-            utiles += pt;
-            ubytes += B_UNSTAGE * J->Vc();
-          }
+        if (J->det()) {
+          it.gout64 = J->det64_pp(dir, s % 2);
+          it.flag64 = J->flag(dir, s);
         }
+        items.push_back(it);
+        owner.push_back(J);
+        bytes += B_EXP_BWD * J->Vc();
       }
     }
-    b.add(ST_PULL_COMBINE, pitems, ptiles, pbytes);
-    b.add(ST_UNSTAGE, uitems, utiles, ubytes);
+    DetLaunch dl;
+    det_assign(dl, items, owner, next_slot);
+    std::vector<DetFoldItem> folds;
+    for (size_t k = 0; k < items.size(); ++k) {
+      Job* J = owner[k];
+      if (!J->det()) continue;
+      ExpBwdItem& it = items[k];
+      it.det_slot = dl.slot[J];
+      it.det_blocks = dl.tiles[J];
+      DetFoldItem f{};
+      f.n = (int)(3 * J->Vc());
+      f.f = it.gout;
+      f.q = it.gout64;
+      f.js = J->js;
+      f.flag = it.flag64;
+      f.det_slot = it.det_slot;
+      f.det_blocks = it.det_blocks;
+      folds.push_back(f);
+    }
+    set_march_tiles(items, tiles);
+    b.add(ST_EXP_BWD, items, tiles, bytes);
+    // the far voxels' pass goes over point tiles
+    tiles = 0;
+    for (ExpBwdItem& it : items) {
+      it.tile0 = tiles;
+      tiles += point_tiles(it.D, it.H, it.W);
+    }
+    add_det_stages(b, ST_EXP_FAR_DETMAX, items, owner);
+    b.add(ST_EXP_FAR, items, tiles, 0.0);
+    add_det_folds(b, folds);
   }
   {
-    // gradients of smoothing jobs: combine into t1 (staged jobs did above),
-    // then smooth t1 -> t2 -> t1 -> t2
-    std::vector<AdamItem> items;
+    // G_0 of both directions into the combined gradient, with the
+    // regularisers; Adam, or the smoothing of the gradient, reads it.  A loss
+    // gradient without smoothing is the result itself.
+    std::vector<CombineItem> items;
     int tiles = 0;
     double bytes = 0;
     for (Job* J : jobs) {
-      if (!J->smoothing() || J->staged()) continue;
-      const size_t V = J->Vc();
+      const int* d = J->ldims[J->level];
       for (int i = 0; i < J->N - 1; ++i) {
-        AdamItem it{};
+        CombineItem it{};
         it.tile0 = tiles;
-        it.n = (int)V;
-        it.g0f = J->pp(2 * i, 0);
-        it.g0b = J->pp(2 * i + 1, 0);
-        it.gout = J->field(J->m_t1.as<float>(), i);
-        it.scale = std::ldexp(1.f, -J->K());
-        it.mode = 2;
+        it.D = d[0]; it.H = d[1]; it.W = d[2];
+        it.gf = J->pp(2 * i, 0);
+        it.gb = J->pp(2 * i + 1, 0);
+        it.out = J->comb(i);
+        it.gmul = 1.f;
+        if (J->grad_direct()) {
+          it.out = J->grad_out + (size_t)i * 3 * J->Vc();
+          it.gmul = J->grad_scale;
+        }
+        it.flow = J->flow(i);
+        it.loss = &J->js->loss_reg;
+        it.reg_w = J->p.alpha_ss / (float)(J->N - 1);
+        it.reg_loss_w = it.reg_w;
+        set_reg_ext(it, *J, i);
         items.push_back(it);
-        tiles += elem_tiles(V);
-        bytes += 36.0 * V;
+        tiles += combine_tiles(d[0], d[1], d[2]);
+        bytes += (B_COMBINE + (it.reg_w != 0.f || it.ext ? 12 : 0)) * J->Vc();
       }
     }
-    b.add(ST_ADAM, items, tiles, bytes);
+    b.add(ST_COMBINE, items, tiles, bytes);
+  }
+  {
+    // the gradients of smoothing jobs: t1 -> t2 -> t1 -> t2
     auto t1 = [](Job* J, int i) { return J->field(J->m_t1.as<float>(), i); };
     auto t2 = [](Job* J, int i) { return J->field(J->m_t2.as<float>(), i); };
     add_smooth_pass(b, jobs, 0, [&](Job* J, int i) { return (const float*)t1(J, i); }, t2);
@@ -1300,20 +1250,16 @@ void add_backward(Builder& b, const std::vector<Job*>& jobs) {
     int tiles = 0;
     double bytes = 0;
     for (Job* J : jobs) {
+      if (J->grad_direct()) continue;
       const size_t V = J->Vc();
       for (int i = 0; i < J->N - 1; ++i) {
         AdamItem it{};
         it.tile0 = tiles;
         it.n = (int)V;
         it.phi = J->field(J->phi, i);
-        it.g0f = J->pp(2 * i, 0);
-        it.g0b = J->pp(2 * i + 1, 0);
-        it.gsrc = J->smoothing() ? J->field(J->m_t2.as<float>(), i)
-                  : J->staged()  ? J->field(J->m_t1.as<float>(), i)
-                                 : nullptr;
+        it.gsrc = J->smoothing() ? J->field(J->m_t2.as<float>(), i) : J->comb(i);
         it.m = J->field(J->mbuf, i);
         it.v = J->field(J->vbuf, i);
-        it.scale = std::ldexp(1.f, -J->K());
         it.mode = J->grad_mode ? 1 : 0;
         it.gout = J->grad_mode ? J->grad_out + (size_t)i * 3 * V : nullptr;
         it.gscale = J->grad_scale;
@@ -1376,10 +1322,10 @@ static int kclass(StageKind k) {
     case ST_RIGID_GRAD: return MUSTER_K_RIGID;
     case ST_RIGID_STEP: return MUSTER_K_RIGID;
     case ST_WARP: return MUSTER_K_WARP;
-    case ST_UNSTAGE: return MUSTER_K_UNSTAGE;
-    case ST_PULL_COMBINE: return MUSTER_K_UNSTAGE;
+    case ST_EXP_FAR: return MUSTER_K_UNSTAGE;
+    case ST_COMBINE: return MUSTER_K_UNSTAGE;
     case ST_COMPOSE_BWD_DETMAX: return MUSTER_K_COMPOSE_BWD;
-    case ST_EXP_BWD_DETMAX: return MUSTER_K_EXP_BWD;
+    case ST_EXP_FAR_DETMAX: return MUSTER_K_UNSTAGE;
     case ST_DET_FOLD: return MUSTER_K_FINISH;
     case ST_DET_CLEAR: return MUSTER_K_FINISH;
   }
@@ -1398,8 +1344,7 @@ static hipError_t launch_stage(const Stage& st, const unsigned char* base, hipSt
       return launch_sim_grad((const SimItem*)p, st.n_items, st.n_tiles, st.window, st.shape, s);
     case ST_COMPOSE_BWD:
       return launch_compose_bwd((const ComposeBwdItem*)p, st.n_items, st.n_tiles, s);
-    case ST_EXP_BWD:
-      return launch_exp_bwd((const ExpBwdItem*)p, st.n_items, st.n_tiles, st.staged, st.reg != 0, s);
+    case ST_EXP_BWD: return launch_exp_bwd((const ExpBwdItem*)p, st.n_items, st.n_tiles, s);
     case ST_ADAM: return launch_adam((const AdamItem*)p, st.n_items, st.n_tiles, s);
     case ST_FINISH: return launch_finish((JobState* const*)p, st.n_items, s);
     case ST_SMOOTH: return launch_smooth((const SmoothItem*)p, st.n_items, st.n_tiles, st.lds, s);
@@ -1409,13 +1354,12 @@ static hipError_t launch_stage(const Stage& st, const unsigned char* base, hipSt
       return launch_rigid_grad((const RigidGradItem*)p, st.n_items, st.n_tiles, s);
     case ST_RIGID_STEP: return launch_rigid_step((const RigidStepItem*)p, st.n_items, s);
     case ST_WARP: return launch_warp((const SimItem*)p, st.n_items, st.n_tiles, s);
-    case ST_UNSTAGE: return launch_unstage((const ExpBwdItem*)p, st.n_items, st.n_tiles, s);
-    case ST_PULL_COMBINE:
-      return launch_pull_combine((const PullItem*)p, st.n_items, st.n_tiles, s);
+    case ST_EXP_FAR: return launch_exp_far((const ExpBwdItem*)p, st.n_items, st.n_tiles, s);
+    case ST_COMBINE: return launch_combine((const CombineItem*)p, st.n_items, st.n_tiles, s);
     case ST_COMPOSE_BWD_DETMAX:
       return launch_compose_bwd_detmax((const ComposeBwdItem*)p, st.n_items, st.n_tiles, s);
-    case ST_EXP_BWD_DETMAX:
-      return launch_exp_bwd_detmax((const ExpBwdItem*)p, st.n_items, st.n_tiles, st.staged, s);
+    case ST_EXP_FAR_DETMAX:
+      return launch_exp_far_detmax((const ExpBwdItem*)p, st.n_items, st.n_tiles, s);
     case ST_DET_FOLD: return launch_det_fold((const DetFoldItem*)p, st.n_items, st.n_tiles, s);
     case ST_DET_CLEAR: return launch_det_clear((JobState* const*)p, st.n_items, s);
   }
@@ -2097,19 +2041,26 @@ muster_status muster_loss_forward(muster_ctx* h, void* stream, int N, const int 
     plan->upload(ctx, s);
     plan->run(ctx, s);
     const GridDims fd{J.ldims[0][0], J.ldims[0][1], J.ldims[0][2]};  // the flow grid
-    for (int i = 0; i < N - 1; ++i)
-      MUSTER_HIP(launch_reg(fd, J.flow(i), &J.js->loss_reg, nullptr, s));
-    for (int i = 0; i < N - 1; ++i) {
-      ExpBwdItem e{};
-      set_reg_ext(e, J, i);
-      if (e.ext)
-        MUSTER_HIP(launch_reg_ext(fd, J.flow(i), e.flow_prev, e.l2_loss_w, e.ts_loss_w, e.inv_dprev,
-                                  e.inv_dself, &J.js->loss_ext, s));
+    {
+      // the regularisers' values alone
+      std::vector<CombineItem> items;
+      int tiles = 0;
+      for (int i = 0; i < N - 1; ++i) {
+        CombineItem it{};
+        it.tile0 = tiles;
+        it.D = fd.D; it.H = fd.H; it.W = fd.W;
+        it.flow = J.flow(i);
+        it.loss = &J.js->loss_reg;
+        it.reg_loss_w = (double)params->alpha_ss / (N - 1);
+        set_reg_ext(it, J, i);
+        items.push_back(it);
+        tiles += combine_tiles(fd.D, fd.H, fd.W);
+      }
+      run_items(ctx, items, tiles, s, launch_combine);
     }
     read_state(J, s);
     if (ctx->timing) resolve_timing(ctx);
-    *loss_host = J.host_state->loss_sim +
-                 (double)params->alpha_ss / (N - 1) * J.host_state->loss_reg + J.host_state->loss_ext;
+    *loss_host = J.host_state->loss_sim + J.host_state->loss_reg;
     auto* sv = new muster_saved;
     sv->ctx = h;
     sv->job = std::move(job);
@@ -2128,6 +2079,7 @@ muster_status muster_loss_backward(muster_ctx* h, void* stream, muster_saved* sa
     Job& J = *saved->job;
     J.grad_out = grad_svf_dev;
     J.grad_scale = (float)grad_out;
+    J.grad_alias = overlap(grad_svf_dev, J.phi, (size_t)(J.N - 1) * 3 * J.Vc());
     std::vector<Job*> one{&J};
     auto plan = build_plan(one, PLAN_LOSS_BWD);
     plan->upload(ctx, s);
@@ -2194,7 +2146,6 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     check_dims(dims, 2);
     NEED(K >= 1 && K <= 20, "K must be in 1..20");
     NEED(sign == 1 || sign == -1, "sign must be +1 or -1");
-    const bool flat_only = (mode & MUSTER_EXP_FLAT) != 0;
     mode &= ~MUSTER_EXP_FLAT;
     NEED(mode == MUSTER_EXP_STORE || mode == MUSTER_EXP_RECOMPUTE, "bad mode");
     std::lock_guard<std::mutex> lk(ctx->mu);
@@ -2203,28 +2154,20 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     const size_t F = 3 * V;
     const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 0) : 2;
     const int tiles = point_tiles(dims[0], dims[1], dims[2]);
-    // the squaring steps exchange their scatter boxes through staging slots,
-    // as in the registration, unless the caller asks for the flat path
-    const bool staged = !flat_only && K >= 2;
-    DevMem us, pp, zero, stage, desc, flags;
+    const int ntp = tiles;
+    // the last step writes grad_svf unless it still reads what lies there
+    const bool direct =
+        !overlap(grad_svf, svf, F) && !(K == 1 && overlap(grad_svf, grad_disp, F));
+    DevMem us, pp, far;
     us.alloc(ctx, std::max<size_t>(nstore, 1) * F * sizeof(float));
     pp.alloc(ctx, 2 * F * sizeof(float));
-    zero.alloc(ctx, F * sizeof(float));
-    MUSTER_HIP(launch_fill(pp.as<float>(), (int64_t)(2 * F), 0.f, sc.s));
-    MUSTER_HIP(launch_fill(zero.as<float>(), (int64_t)F, 0.f, sc.s));
-    if (staged) {
-      stage.alloc(ctx, (size_t)2 * tiles * 3 * STAGE_CAP * sizeof(float));
-      desc.alloc(ctx, (size_t)2 * tiles * 8 * sizeof(int));
-      flags.alloc(ctx, (size_t)K * sizeof(int));
-      // zero bits: the overflow flags start clear
-      MUSTER_HIP(launch_fill(flags.as<float>(), (int64_t)K, 0.f, sc.s));
-    }
-    auto st_slot = [&](int k) { return stage.as<float>() + (size_t)k * tiles * 3 * STAGE_CAP; };
-    auto de_slot = [&](int k) { return desc.as<int>() + (size_t)k * tiles * 8; };
+    far.alloc(ctx, (size_t)ntp * sizeof(int));
+    // zero bits: the marks start clear
+    MUSTER_HIP(launch_fill(far.as<float>(), (int64_t)ntp, 0.f, sc.s));
     const float a0 = (float)sign * std::ldexp(1.f, -K);
     auto ustore = [&](int k) { return us.as<float>() + (size_t)(k - 1) * F; };        // store: u_k
     auto uscr = [&](int k) { return us.as<float>() + (size_t)((k - 1) % 2) * F; };    // recompute
-    struct L { int kind; size_t off; int smode; };
+    struct L { int kind; size_t off; int tiles; };
     std::vector<L> seq;
     auto fwd_step = [&](int k, float* src, float* dst) {
       ExpFwdItem it{};
@@ -2232,7 +2175,7 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
       it.src = k == 0 ? svf : src;
       it.a = k == 0 ? a0 : 1.f;
       it.dst = dst;
-      seq.push_back({0, sc.add(it), 0});
+      seq.push_back({0, sc.add(it), tiles});
     };
     if (mode == MUSTER_EXP_STORE)
       for (int k = 0; k < K - 1; ++k) fwd_step(k, k == 0 ? nullptr : ustore(k), ustore(k + 1));
@@ -2246,53 +2189,31 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
         for (int k = 0; k < s; ++k) fwd_step(k, k == 0 ? nullptr : uscr(k), uscr(k + 1));
         us_src = uscr(s);
       }
-      ExpBwdItem it{};
+      std::vector<ExpBwdItem> one(1);
+      ExpBwdItem& it = one[0];
+      it = ExpBwdItem{};
       it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
       it.src = us_src;
-      it.a = s == 0 ? a0 : 1.f;
-      it.gin = s == K - 1 ? const_cast<float*>(grad_disp) : pp.as<float>() + (size_t)((s + 1) % 2) * F;
-      it.gout = pp.as<float>() + (size_t)(s % 2) * F;
-      it.zero_in = s < K - 1 ? 1 : 0;
-      const bool in_st = staged && s < K - 1;
-      if (in_st) {
-        it.stage_in = st_slot((s + 1) % 2);
-        it.desc_in = de_slot((s + 1) % 2);
-        it.flag_in = flags.as<int>() + s + 1;
-      }
-      if (staged) {
-        it.stage_out = st_slot(s % 2);
-        it.desc_out = de_slot(s % 2);
-        it.flag_out = flags.as<int>() + s;
-      }
-      seq.push_back({1, sc.add(it), in_st ? 2 : (staged ? 1 : 0)});
+      it.a = it.oscale = s == 0 ? a0 : 1.f;
+      it.gin = s == K - 1 ? grad_disp : pp.as<float>() + (size_t)((s + 1) % 2) * F;
+      it.gout = s == 0 && direct ? grad_svf : pp.as<float>() + (size_t)(s % 2) * F;
+      it.far = far.as<int>();
+      int mt = 0;
+      set_march_tiles(one, mt);
+      seq.push_back({1, sc.add(it), mt});
     }
-    if (staged) {
-      // the staged G_0 to the flat field, as k_unstage does in the registration
-      ExpBwdItem it{};
-      it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
-      it.gout = pp.as<float>();
-      it.stage_in = st_slot(0);
-      it.desc_in = de_slot(0);
-      it.flag_in = flags.as<int>();
-      seq.push_back({3, sc.add(it), 0});
-    }
-    AdamItem ai{};
-    ai.n = (int)V;
-    ai.g0f = pp.as<float>();
-    ai.g0b = zero.as<float>();
-    ai.gout = grad_svf;
-    ai.scale = a0;
-    ai.gscale = 1.f;
-    ai.mode = 1;
-    seq.push_back({2, sc.add(ai), 0});
     sc.upload();
     for (auto& l : seq) {
       const unsigned char* p = sc.dev() + l.off;
-      if (l.kind == 0) MUSTER_HIP(launch_exp_fwd((const ExpFwdItem*)p, 1, tiles, sc.s));
-      if (l.kind == 1) MUSTER_HIP(launch_exp_bwd((const ExpBwdItem*)p, 1, tiles, l.smode, false, sc.s));
-      if (l.kind == 3) MUSTER_HIP(launch_unstage((const ExpBwdItem*)p, 1, tiles, sc.s));
-      if (l.kind == 2) MUSTER_HIP(launch_adam((const AdamItem*)p, 1, elem_tiles(V), sc.s));
+      if (l.kind == 0) {
+        MUSTER_HIP(launch_exp_fwd((const ExpFwdItem*)p, 1, l.tiles, sc.s));
+      } else {
+        MUSTER_HIP(launch_exp_bwd((const ExpBwdItem*)p, 1, l.tiles, sc.s));
+        MUSTER_HIP(launch_exp_far((const ExpBwdItem*)p, 1, ntp, sc.s));
+      }
     }
+    if (!direct)
+      MUSTER_HIP(hipMemcpyAsync(grad_svf, pp.p, F * sizeof(float), hipMemcpyDeviceToDevice, sc.s));
     MUSTER_HIP(hipStreamSynchronize(sc.s));
   });
 }
@@ -2473,11 +2394,21 @@ muster_status muster_reg(muster_ctx* h, void* stream, const int dims[3], const f
     NEED(ctx && phi && reg_host, "NULL argument");
     check_dims(dims, 2);
     std::lock_guard<std::mutex> lk(ctx->mu);
-    hipStream_t s = (hipStream_t)stream;
-    MUSTER_HIP(hipMemsetAsync(ctx->step_acc, 0, sizeof(double), s));
-    MUSTER_HIP(launch_reg(GridDims{dims[0], dims[1], dims[2]}, phi, ctx->step_acc, grad, s));
-    MUSTER_HIP(hipMemcpyAsync(reg_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, s));
-    MUSTER_HIP(hipStreamSynchronize(s));
+    StepCall sc{ctx, (hipStream_t)stream, {}};
+    CombineItem it{};
+    it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
+    it.flow = phi;
+    it.out = grad;
+    it.gmul = it.reg_w = 1.f;
+    it.loss = ctx->step_acc;
+    it.reg_loss_w = 1.0;
+    const size_t off = sc.add(it);
+    sc.upload();
+    MUSTER_HIP(hipMemsetAsync(ctx->step_acc, 0, sizeof(double), sc.s));
+    MUSTER_HIP(launch_combine((const CombineItem*)(sc.dev() + off), 1,
+                              combine_tiles(dims[0], dims[1], dims[2]), sc.s));
+    MUSTER_HIP(hipMemcpyAsync(reg_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, sc.s));
+    MUSTER_HIP(hipStreamSynchronize(sc.s));
   });
 }
 

@@ -141,6 +141,9 @@ struct Job {
   bool grad_mode = false;            // autograd: phi is the caller's, Adam writes a gradient
   float* grad_out = nullptr;
   float grad_scale = 1.f;
+  bool grad_alias = false;           // grad_out shares memory with phi
+  // the combination writes the loss gradient itself
+  bool grad_direct() const { return grad_mode && !smoothing() && !grad_alias; }
 
   int level = 0;                     // current pyramid level (0 = coarsest)
   int ff = 1;                        // flow grid factor: flows on the image grid / ff
@@ -155,8 +158,8 @@ struct Job {
   DevMem m_pimg, m_gimg;             // pair fields and their gradients on the image grid (ff > 1)
   DevMem m_rigid;                    // RigidState of sessions 1..N-1 (params.rigid)
   float* rigid_out = nullptr;
-  DevMem m_stage, m_desc, m_flags;   // staged Exp-backward accumulation (K >= 2)
-  DevMem m_det64;                    // deterministic mode: fixed-point twins (see det64_*)
+  DevMem m_far;                      // Exp backward: marks of k_exp_far per direction and point tile
+  DevMem m_det64, m_flags;           // deterministic mode: fixed-point twins (see det64_*), flags
   float* phi = nullptr;              // may alias the caller's field in grad_mode
   float* mbuf = nullptr;
   float* vbuf = nullptr;
@@ -189,12 +192,13 @@ struct Job {
   RigidState* rigid(int j) const { return m_rigid.as<RigidState>() + (j - 1); }  // j >= 1
   float* pair_grad_img(int i, int j) const;
   float* pp(int dir, int k) const { return field(m_pp.as<float>(), (size_t)dir * 2 + k); }
-  bool staged() const { return p.K >= 2; }
-  int tiles_fine = 0;                // point tiles of the finest grid
-  float* stage(int dir, int k) const {
-    return m_stage.as<float>() + ((size_t)dir * 2 + k) * tiles_fine * 3 * STAGE_CAP;
+  // the combined gradient of interval i that Adam, or its smoothing, reads
+  // (K = 1 leaves the second ping-pong field free)
+  float* comb(int i) const {
+    return smoothing() || p.K >= 2 ? field(m_t1.as<float>(), (size_t)i) : pp(2 * i, 1);
   }
-  int* desc(int dir, int k) const { return m_desc.as<int>() + ((size_t)dir * 2 + k) * tiles_fine * 8; }
+  int tiles_fine = 0;                // point tiles of the finest grid
+  int* far(int dir) const { return m_far.as<int>() + (size_t)dir * tiles_fine; }
   int* flag(int dir, int s) const { return m_flags.as<int>() + (size_t)dir * p.K + s; }
   bool det() const { return p.deterministic != 0; }
   // 64-bit fixed-point twins of the gradient of consecutive field dir (the
@@ -226,7 +230,7 @@ void load_tune_cache(Ctx* ctx);
 enum StageKind {
   ST_EXP_FWD, ST_COMPOSE_FWD, ST_SIM_STATS, ST_SIM_GRAD, ST_COMPOSE_BWD, ST_EXP_BWD, ST_ADAM,
   ST_FINISH, ST_SMOOTH, ST_UPSAMPLE, ST_UPSAMPLE_ADJ, ST_RIGID_GRAD, ST_RIGID_STEP, ST_WARP,
-  ST_UNSTAGE, ST_PULL_COMBINE, ST_COMPOSE_BWD_DETMAX, ST_EXP_BWD_DETMAX, ST_DET_FOLD,
+  ST_EXP_FAR, ST_COMBINE, ST_COMPOSE_BWD_DETMAX, ST_EXP_FAR_DETMAX, ST_DET_FOLD,
   ST_DET_CLEAR
 };
 
@@ -236,8 +240,6 @@ struct Stage {
   int n_items;
   int n_tiles;
   int window = 0, metric = 0, zc = 32;
-  int staged = 0;    // Exp-backward staging mode
-  int reg = 0;       // Exp backward: some item adds regulariser terms
   int lds = 0;       // dynamic LDS floats (smoothing)
   int shape = 0;     // window-statistics tile shape
   double bytes = 0;  // algorithmic bytes of the launch
