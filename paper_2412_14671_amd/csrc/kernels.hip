@@ -495,36 +495,6 @@ __device__ __forceinline__ void sample_cells_lds(const cgfloat* __restrict__ f, 
 }
 
 // ---------------------------------------------------------------------------
-// Exp forward: one squaring u' = u + u o (Omega + u)   (Alg. 1)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) GATHER_WAVES void k_exp_fwd(const ExpFwdItem* __restrict__ items,
-                                                   int n_items, int n_tiles) {
-  const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const ExpFwdItem it = items[find_item(items, n_items, tile)];
-  const int D = it.D, H = it.H, W = it.W, V = D * H * W;
-  const PTile tc = point_tile(tile - it.tile0, H, W);
-  const float a = it.a;
-  const cgfloat* __restrict__ s = gp(it.src);
-  gfloat* __restrict__ d = gp(it.dst);
-  __shared__ float box[3 * GATHER_CELLS];
-  __shared__ int sred[8 * (BLOCK / 64)];
-  VoxSet vs;
-  vox_set(tc, D, H, W, vs);
-  float uu[VPT][3];
-  CellSet cs;
-  load_cells(s, a, D, H, W, vs, uu, cs);
-  float sm[VPT][3];
-  sample_cells_lds(s, V, H, W, vs, cs, box, sred, sm);
-#pragma unroll
-  for (int j = 0; j < VPT; ++j) {
-    if (!vs.ok[j]) continue;
-    sto(d, vs.p[j], uu[j][0] + a * sm[j][0]);
-    sto(d + V, vs.p[j], uu[j][1] + a * sm[j][1]);
-    sto(d + 2 * V, vs.p[j], uu[j][2] + a * sm[j][2]);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Composition forward: out = prev + C o (Omega + prev)   (Eq. cum_deformation)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) GATHER_WAVES void k_compose_fwd(const ComposeItem* __restrict__ items,
@@ -837,6 +807,107 @@ __device__ __forceinline__ bool is_near(const float (&e)[3]) {
 }
 
 // ---------------------------------------------------------------------------
+// Exp forward: one squaring u' = u + u o (Omega + u)   (Alg. 1)
+//
+// The corners of a near voxel's cell come from a ring of the last planes of u
+// in LDS; a voxel that samples a voxel or more away reads its corners from
+// memory.  Values and arithmetic are the same either way.
+//
+// Bound by memory: 24 bytes per voxel at 4 TB/s, the planes' halo coming from
+// cache.  Against a box of sampled cells found and loaded per 8 x 8 x 16 tile
+// (187 vector instructions per voxel, about 100 here): one 160x192x160 field
+// 34.0 -> 28.3 us, six of them at once 38.7 -> 29.8 us per field.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(MT_NT) void k_exp_fwd(const ExpFwdItem* __restrict__ items,
+                                                   int n_items, int n_tiles) {
+  constexpr int PX = MT_PX, ROW = 3 * PX, PLANE = MT_PY * ROW;
+  __shared__ float up[4 * PLANE];  // a * src of the last planes, [plane & 3][row][component][column]
+  const int tile = xcd_remap(blockIdx.x, n_tiles);
+  const ExpFwdItem it = items[find_item(items, n_items, tile)];
+  const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
+  const MTile tc = march_tile(tile - it.tile0, D, H, W, it.zc);
+  const float a = it.a;
+  const Planes<const cgfloat> sp(gp(it.src), V);
+  const Planes<gfloat> dp(gp(it.dst), V);
+  const int ly = threadIdx.x / MT_X, lx = threadIdx.x % MT_X;
+  const int y = tc.y0 + ly, x = tc.x0 + lx;
+  const MCol own = march_col(tc, ly + 1, lx + 1, H, W);
+  const bool ring = threadIdx.x < MT_RING;
+  int rrow = 0, rcol = 0;
+  if (ring) ring_site(threadIdx.x, rrow, rcol);
+  const MCol rim = march_col(tc, rrow, rcol, H, W);
+  float* const own_up = up + (ly + 1) * ROW + lx + 1;
+  float* const rim_up = up + rrow * ROW + rcol;
+  auto load = [&](int z, const MCol& m, float (&u)[3]) {
+    const uint32_t p = (uint32_t)(min(max(z, 0), D - 1) * HW) + m.off;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) u[c] = ldo(sp.c[c], p);
+  };
+  float nu[3], ru[3], pu[3] = {0.f, 0.f, 0.f}, res[3];
+  load(tc.z0 - 1, own, nu);
+  if (ring) load(tc.z0 - 1, rim, ru);
+  for (int zp = tc.z0 - 1;; ++zp) {
+    // plane zp into the ring: its slot was last read two passes ago
+    float cu[3];
+    const int slot = (zp & 3) * PLANE;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      cu[c] = a * nu[c];
+      own_up[slot + c * PX] = cu[c];
+    }
+    if (ring) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rim_up[slot + c * PX] = a * ru[c];
+    }
+    __syncthreads();
+    // the last pass's results before the next plane's loads (see k_exp_bwd)
+    if (zp - 2 >= tc.z0 && own.in) {
+      const uint32_t p = (uint32_t)((zp - 2) * HW) + own.off;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sto(dp.c[c], p, res[c]);
+    }
+    if (zp > tc.z1) break;
+    if (zp < tc.z1) {
+      load(zp + 1, own, nu);
+      if (ring) load(zp + 1, rim, ru);
+    }
+    const int zo = zp - 1;
+    if (zo >= tc.z0 && own.in) {
+      float e[3];
+      hold(pu, zo, D, own, e);
+      if (is_near(e)) {
+        const bool bz = e[0] < 0.f || zo == D - 1, by = e[1] < 0.f || y == H - 1,
+                   bx = e[2] < 0.f || x == W - 1;
+        const int q = (ly + 1 - (by ? 1 : 0)) * ROW + lx + 1 - (bx ? 1 : 0);
+        const float* q0 = up + ((bz ? zo - 1 : zo) & 3) * PLANE + q;
+        const float* q1 = up + ((bz ? zo : zo + 1) & 3) * PLANE + q;
+        const float tz = e[0] + (bz ? 1.f : 0.f), ty = e[1] + (by ? 1.f : 0.f),
+                    tx = e[2] + (bx ? 1.f : 0.f);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const int o = c * PX;
+          const float v[8] = {q0[o], q0[o + 1], q0[o + ROW], q0[o + ROW + 1],
+                              q1[o], q1[o + 1], q1[o + ROW], q1[o + ROW + 1]};
+          res[c] = pu[c] + tri_val(v, tz, ty, tx);
+        }
+      } else {
+        const Ax az = axis_disp(zo, pu[0], D), ay = axis_disp(y, pu[1], H),
+                 ax = axis_disp(x, pu[2], W);
+        const int base = (az.i0 * H + ay.i0) * W + ax.i0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          float v[8];
+          load8(sp.c[c], base, W, HW, v);
+          res[c] = pu[c] + a * tri_val(v, az.t, ay.t, ax.t);
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) pu[c] = cu[c];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Exp backward: one squaring, dL/du_s from dL/du_{s+1}
 //   G_s(p) = G(p) + J_u(q)^T G(p) + sum_{p': corners of q(p') contain p} w G(p')
 // scaled by the item's oscale.
@@ -859,8 +930,9 @@ __device__ __forceinline__ bool is_near(const float (&e)[3]) {
 // of scatter boxes in LDS that this replaced took 512 and moved 60 bytes per
 // voxel against 43 (the columns' halo included).  160x192x160, K 7, the whole
 // adjoint with its forward steps: 975 -> 672 us, and the error against 64 bits
-// 1.2e-5 -> 1.3e-7.  16 x 16 columns: 1.27 columns are loaded per column owned,
-// and five blocks share a CU (31 KB of LDS, 90 VGPRs).
+// 1.2e-5 -> 1.3e-7.  8 x 32 columns: whole 128-byte lines per row and no bank
+// conflicts between a wave's rows; six 160x192x160 fields at once take 284 us,
+// with 16 x 16 columns 361, with 16 x 32 300, with 8 x 16 403, with 4 x 64 324.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const ExpBwdItem* __restrict__ items,
                                                    int n_items, int n_tiles) {
@@ -938,26 +1010,35 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const ExpBwdItem* __restrict_
       if (ring) load(zp + 1, rim, ru, rg);
     }
     if (in_z) {
-      const float4* qa = ra[zp & 1] + own.place;
-      const float2* qb = rb[zp & 1] + own.place;
+      // first column of the 3 x 3 around the own one, so that every offset
+      // is an immediate one
+      const float4* qa = ra[zp & 1] + (own.place - PX - 1);
+      const float2* qb = rb[zp & 1] + (own.place - PX - 1);
+      // what goes to plane zp - 1, to zp + 1, and to all three: the hats of
+      // an axis sum to one
+      float dn[3] = {0.f, 0.f, 0.f}, all[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-      for (int dy = -1; dy <= 1; ++dy)
+      for (int dy = 0; dy <= 2; ++dy)
 #pragma unroll
-        for (int dx = -1; dx <= 1; ++dx) {
+        for (int dx = 0; dx <= 2; ++dx) {
           const float4 A = qa[dy * PX + dx];
           const float2 B = qb[dy * PX + dx];
-          const float hy = dy ? unit(dy < 0 ? A.y : -A.y) : 1.f - fabsf(A.y);
-          const float hx = dx ? unit(dx < 0 ? A.z : -A.z) : 1.f - fabsf(A.z);
-          const float w = hy * hx;
-          const float g[3] = {w * A.w, w * B.x, w * B.y};
-          const float hm = unit(-A.x), h0 = 1.f - fabsf(A.x), hp = unit(A.x);
+          const float hy = dy == 1 ? 1.f - fabsf(A.y) : unit(dy < 1 ? A.y : -A.y);
+          const float hx = dx == 1 ? 1.f - fabsf(A.z) : unit(dx < 1 ? A.z : -A.z);
+          const float w = hy * hx, wd = w * unit(-A.x), wu = w * unit(A.x);
+          const float g[3] = {A.w, B.x, B.y};
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            s0[c] = fmaf(hm, g[c], s0[c]);
-            s1[c] = fmaf(h0, g[c], s1[c]);
-            s2[c] = fmaf(hp, g[c], s2[c]);
+            all[c] = fmaf(w, g[c], all[c]);
+            dn[c] = fmaf(wd, g[c], dn[c]);
+            s2[c] = fmaf(wu, g[c], s2[c]);
           }
         }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        s0[c] += dn[c];
+        s1[c] += all[c] - dn[c] - s2[c];
+      }
     }
     const int zo = zp - 1;
     if (zo >= tc.z0 && own.in) {
@@ -1144,19 +1225,25 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const CombineItem* __re
           xm[c] = x > 0 ? ldo(q, p - 1) : 0.f;
           xp[c] = x + 1 < W ? ldo(q, p + 1) : 0.f;
         }
+        // squares summed in float over the components of one voxel, in double
+        // beyond (a conversion per square would be the longest part)
+        float vz = 0.f, vy = 0.f, vx = 0.f;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           float rg = 0.f;
-          if (z + 1 < D) { const float d = fp[c] - fc[c]; rg -= 2.f * d * inv_mz; sz = fma((double)d, (double)d, sz); }
+          if (z + 1 < D) { const float d = fp[c] - fc[c]; rg -= 2.f * d * inv_mz; vz = fmaf(d, d, vz); }
           if (z > 0)     { const float d = fc[c] - fm[c]; rg += 2.f * d * inv_mz; }
-          if (y + 1 < H) { const float d = yp[c] - fc[c]; rg -= 2.f * d * inv_my; sy = fma((double)d, (double)d, sy); }
+          if (y + 1 < H) { const float d = yp[c] - fc[c]; rg -= 2.f * d * inv_my; vy = fmaf(d, d, vy); }
           if (y > 0)     { const float d = fc[c] - ym[c]; rg += 2.f * d * inv_my; }
-          if (x + 1 < W) { const float d = xp[c] - fc[c]; rg -= 2.f * d * inv_mx; sx = fma((double)d, (double)d, sx); }
+          if (x + 1 < W) { const float d = xp[c] - fc[c]; rg -= 2.f * d * inv_mx; vx = fmaf(d, d, vx); }
           if (x > 0)     { const float d = fc[c] - xm[c]; rg += 2.f * d * inv_mx; }
           g[c] = fmaf(it.reg_w, rg, g[c]);
           fm[c] = fc[c];
           fc[c] = fp[c];
         }
+        sz += (double)vz;
+        sy += (double)vy;
+        sx += (double)vx;
       }
       if (it.ext) {
         // L_L2 and L_ts (Sec. 2.4): linear in the flows of this interval and its neighbours
@@ -2283,7 +2370,7 @@ void set_launch_events(hipEvent_t start, hipEvent_t stop) {
 
 hipError_t launch_exp_fwd(const ExpFwdItem* items, int n_items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_exp_fwd, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_items, n_tiles);
+  MUSTER_LAUNCH(k_exp_fwd, dim3(n_tiles), dim3(MT_NT), 0, s, items, n_items, n_tiles);
   return hipGetLastError();
 }
 

@@ -53,7 +53,7 @@ struct ExpFwdItem {
   const float* src;
   float* dst;
   float a;
-  int pad;
+  int zc;            // planes per march tile
 };
 
 // out = prev + C o (Omega + prev).
@@ -316,7 +316,7 @@ constexpr int PT_VOX = PT_Z * PT_Y * PT_X;
 constexpr int BLOCK = 256;
 constexpr int SCATTER_CELLS = 2048;          // LDS bins per component
 // Columns of a marching block (y, x), and the marks a block of k_exp_far reads.
-constexpr int MT_Y = 16, MT_X = 16;
+constexpr int MT_Y = 8, MT_X = 32;
 constexpr int FAR_GROUP = 8;
 constexpr int MARCH_BLOCKS = 1024;             // blocks that fill the chip
 // Tiles of the combination of the SVF gradients.

@@ -742,6 +742,22 @@ void add_smooth_flow(Builder& b, const std::vector<Job*>& jobs) {
 }
 
 
+// Planes per march tile of a launch over these items: the longest chunk that
+// still fills the chip.
+template <class Item>
+void set_march_tiles(std::vector<Item>& items, int& tiles) {
+  int zc = 64;
+  do {
+    zc /= 2;
+    tiles = 0;
+    for (Item& it : items) {
+      it.zc = zc;
+      it.tile0 = tiles;
+      tiles += march_tiles(it.D, it.H, it.W, zc);
+    }
+  } while (zc > 2 && tiles < MARCH_BLOCKS);
+}
+
 void add_exp_fwd_step(Builder& b, const std::vector<Job*>& jobs, int s, bool recompute_only,
                       int upto) {
   // One squaring s -> s+1 for every direction of every job.  With
@@ -769,10 +785,10 @@ void add_exp_fwd_step(Builder& b, const std::vector<Job*>& jobs, int s, bool rec
       }
       it.dst = J->u_step(dir, s + 1);
       items.push_back(it);
-      tiles += point_tiles(d[0], d[1], d[2]);
       bytes += B_EXP_FWD * J->Vc();
     }
   }
+  set_march_tiles(items, tiles);
   b.add(ST_EXP_FWD, items, tiles, bytes);
 }
 
@@ -991,22 +1007,6 @@ void set_reg_ext(CombineItem& it, const Job& J, int i) {
   it.w_self = (float)w_self;
   it.w_prev = (float)w_prev;
   it.w_next = (float)w_next;
-}
-
-// Planes per march tile of a launch over these items: the longest chunk that
-// still fills the chip.
-template <class Item>
-void set_march_tiles(std::vector<Item>& items, int& tiles) {
-  int zc = 64;
-  do {
-    zc /= 2;
-    tiles = 0;
-    for (Item& it : items) {
-      it.zc = zc;
-      it.tile0 = tiles;
-      tiles += march_tiles(it.D, it.H, it.W, zc);
-    }
-  } while (zc > 2 && tiles < MARCH_BLOCKS);
 }
 
 // Deterministic jobs' part of a scatter launch: the job's tiles in it (the
@@ -2117,15 +2117,17 @@ muster_status muster_exp(muster_ctx* h, void* stream, const int dims[3], int K, 
       if (steps) return steps + (size_t)(k - 1) * 3 * V;
       return tmp.as<float>() + (size_t)((k - 1) % 2) * 3 * V;
     };
-    const int tiles = point_tiles(dims[0], dims[1], dims[2]);
+    int tiles = 0;
     std::vector<size_t> offs;
     for (int s = 0; s < K; ++s) {
-      ExpFwdItem it{};
-      it.tile0 = 0;
+      std::vector<ExpFwdItem> one(1);
+      ExpFwdItem& it = one[0];
+      it = ExpFwdItem{};
       it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
       it.src = s == 0 ? svf : buf(s);
       it.a = s == 0 ? (float)sign * std::ldexp(1.f, -K) : 1.f;
       it.dst = s == K - 1 ? disp : buf(s + 1);
+      set_march_tiles(one, tiles);
       offs.push_back(sc.add(it));
     }
     sc.upload();
@@ -2153,8 +2155,7 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     const size_t V = (size_t)dims[0] * dims[1] * dims[2];
     const size_t F = 3 * V;
     const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 0) : 2;
-    const int tiles = point_tiles(dims[0], dims[1], dims[2]);
-    const int ntp = tiles;
+    const int ntp = point_tiles(dims[0], dims[1], dims[2]);
     // the last step writes grad_svf unless it still reads what lies there
     const bool direct =
         !overlap(grad_svf, svf, F) && !(K == 1 && overlap(grad_svf, grad_disp, F));
@@ -2170,12 +2171,16 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     struct L { int kind; size_t off; int tiles; };
     std::vector<L> seq;
     auto fwd_step = [&](int k, float* src, float* dst) {
-      ExpFwdItem it{};
+      std::vector<ExpFwdItem> one(1);
+      ExpFwdItem& it = one[0];
+      it = ExpFwdItem{};
       it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
       it.src = k == 0 ? svf : src;
       it.a = k == 0 ? a0 : 1.f;
       it.dst = dst;
-      seq.push_back({0, sc.add(it), tiles});
+      int mt = 0;
+      set_march_tiles(one, mt);
+      seq.push_back({0, sc.add(it), mt});
     };
     if (mode == MUSTER_EXP_STORE)
       for (int k = 0; k < K - 1; ++k) fwd_step(k, k == 0 ? nullptr : ustore(k), ustore(k + 1));
