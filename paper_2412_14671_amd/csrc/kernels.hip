@@ -1455,18 +1455,22 @@ __global__ void k_det_clear(JobState* const* __restrict__ states, int n_jobs) {
 }
 
 // ---------------------------------------------------------------------------
-// Windowed statistics (Sec. 2.6): warp + LNCC/SiLNCC per window, loss and
-// the per-window adjoint coefficients.
+// Window sums of the coefficients.  A block of TY x TX threads owns as many
+// columns of the grid and walks a chunk of z.  For every input slice, the
+// (TY + 2r) x (TX + 2r) patch around the columns goes to LDS, is summed over x
+// there in segments of 8 outputs (a sliding sum from 8 + 2r values read once),
+// and each thread then sums 2r + 1 of the x-sums along y for its own column.
+// The sums over z need no subtraction and no moving ring: slices are taken in
+// groups of w = 2r + 1, and a window that ends inside a group is the sum of
+// that group so far plus a suffix sum of the group before, so a column keeps w
+// values per quantity at fixed registers (the loop is unrolled over a group).
 //
-// The source image is first warped by the pair field once per voxel
-// (k_warp).  A block of the statistics owns TY x TX window centres in (y, x)
-// and marches through a chunk of z.  Every thread owns a few columns of the
-// (TY + 2r) x (TX + 2r) patch around them.  For each input slice it reads the
-// fixed and the warped image at its columns and keeps the last w slices of
-// its per-column values in registers with their running sums over z.  For
-// every centre slice the z-sums go to LDS and are summed over x, then over y
-// (box_x, box_y).  Values are shifted by one per-block constant before the
-// products, which keeps the variance differences well conditioned.
+// The stages work on several slices at once (loading n + 3, storing n + 2,
+// summing n + 1 over x, and n over y and z) in two buffers, with one barrier per
+// slice.  Bound by memory: 12 pairs of 160x192x160 at w 7 move 3.0 GB
+// (coefficients with their halo, field, images, gradient) at 4.7 TB/s: 1040 ->
+// 640 us against z-sums of every patch column in a moving ring first, at three
+// barriers per slice.
 // ---------------------------------------------------------------------------
 struct STile {
   int z0, z1, y0, x0;
@@ -1485,76 +1489,46 @@ __device__ __forceinline__ STile stat_tile(int local, int D, int H, int W, int z
   return t;
 }
 
-// Geometry of the window sums of Q quantities.  A block of TY x TX threads;
-// thread t owns the patch columns t + k * NT.  LDS holds, per quantity, the
-// z-sums of the patch (rows of PXS floats), their x-sums (PY rows of TXS
-// floats) and the finished sums of the centres (TY x TX).  The row strides
-// are odd, so the rows a wave walks along fall in distinct banks.  The x and
-// y passes give each thread a segment of 8 outputs: it reads the 8 + 2r
-// inputs once and forms the 8 sums from registers as a sliding sum.
-template <int R, int TY, int TX, int Q>
-struct Box {
-  static constexpr int NT = TY * TX, RW = R, TXO = TX;
-  static constexpr int WN = 2 * R + 1;
-  static constexpr int PY = TY + 2 * R, PX = TX + 2 * R, P1 = PY * PX;
-  static constexpr int NS = (P1 + NT - 1) / NT;
-  static constexpr int PXS = PX | 1, TXS = TX + 1;
-  static constexpr int SX = 8, SY = 8, NXS = TX / SX, NYS = TY / SY;
-  static constexpr int ZQ = PY * PXS, XQ = PY * TXS, YQ = TY * TX;
-  static constexpr int LDS = Q * (ZQ + XQ + YQ);
-  static_assert(TX % SX == 0 && TY % SY == 0, "tile not a multiple of the segments");
+template <int R, int TY, int TX>
+struct Win {
+  static constexpr int NT = TY * TX, WN = 2 * R + 1;
+  static constexpr int PY = TY + 2 * R, PX = TX + 2 * R;
+  static constexpr int PXS = PX | 1;              // odd: the rows a wave reads fall in distinct banks
+  static constexpr int SITES = PY * PXS;          // patch slots, the odd padding included
+  static constexpr int NS = (SITES + NT - 1) / NT;
+  static constexpr int SLICE = NS * NT;           // floats of one loaded slice in LDS
+  static constexpr int SEG = 8, NSEG = TX / SEG, XT = PY * NSEG;  // x-sum tasks of one quantity
+  static constexpr int TXS = TX + 1, XQ = PY * TXS;
+  static_assert(TX % SEG == 0, "tile not a multiple of the segments");
 };
 
-// x-sums of the window: xs[q][row][c] = sum_k zs[q][row][c + k].
-template <class B>
-__device__ __forceinline__ void box_x(const float* __restrict__ zs, float* __restrict__ xs, int Q) {
-  constexpr int R = B::RW, WN = B::WN, SX = B::SX, PY = B::PY, NXS = B::NXS;
-  const int n = Q * PY * NXS;
-  for (int e = threadIdx.x; e < n; e += B::NT) {
-    const int q = e / (PY * NXS), r = e - q * (PY * NXS);
-    // segments fastest across lanes: with the odd row stride, the lanes of a
-    // half wave read and write distinct banks
-    const int row = r / NXS, seg = r - row * NXS;
-    const float* s = zs + q * B::ZQ + row * B::PXS + seg * SX;
-    float* d = xs + q * B::XQ + row * B::TXS + seg * SX;
-    float v[SX + 2 * R];
+// Sliding sums of WN consecutive values of v, 8 of them, to d at a stride.
+template <int WN, int STRIDE>
+__device__ __forceinline__ void slide8(const float (&v)[7 + WN], float* __restrict__ d) {
+  float acc = v[0];
 #pragma unroll
-    for (int k = 0; k < SX + 2 * R; ++k) v[k] = s[k];
-    float acc = v[0];
+  for (int k = 1; k < WN; ++k) acc += v[k];
+  d[0] = acc;
 #pragma unroll
-    for (int k = 1; k < WN; ++k) acc += v[k];
-    d[0] = acc;
-#pragma unroll
-    for (int i = 1; i < SX; ++i) {
-      acc += v[i + 2 * R] - v[i - 1];
-      d[i] = acc;
-    }
+  for (int i = 1; i < 8; ++i) {
+    acc += v[i + WN - 1] - v[i - 1];
+    d[i * STRIDE] = acc;
   }
 }
 
-// y-sums of the x-sums: ys[q][y][c] = sum_k xs[q][y + k][c].
-template <class B>
-__device__ __forceinline__ void box_y(const float* __restrict__ xs, float* __restrict__ ys, int Q) {
-  constexpr int R = B::RW, WN = B::WN, SY = B::SY, TX = B::TXO, NYS = B::NYS, TXS = B::TXS;
-  const int n = Q * TX * NYS;
-  for (int e = threadIdx.x; e < n; e += B::NT) {
-    const int q = e / (TX * NYS), r = e - q * (TX * NYS);
-    const int seg = r / TX, x = r - seg * TX;
-    const float* s = xs + q * B::XQ + seg * SY * TXS + x;
-    float* d = ys + q * B::YQ + seg * SY * TX + x;
-    float v[SY + 2 * R];
+// Sum over the last WN values of a column, v being value j of its group: ring
+// holds, at j and above, the suffix sums of the group before, and below j the
+// group's own values; pre is the group's sum so far.
+template <int WN>
+__device__ __forceinline__ float window_sum(float (&ring)[WN], float& pre, int j, float v) {
+  pre = j == 0 ? v : pre + v;
+  const float s = j + 1 < WN ? pre + ring[j + 1 < WN ? j + 1 : 0] : pre;
+  ring[j] = v;
+  if (j == WN - 1) {
 #pragma unroll
-    for (int k = 0; k < SY + 2 * R; ++k) v[k] = s[k * TXS];
-    float acc = v[0];
-#pragma unroll
-    for (int k = 1; k < WN; ++k) acc += v[k];
-    d[0] = acc;
-#pragma unroll
-    for (int i = 1; i < SY; ++i) {
-      acc += v[i + 2 * R] - v[i - 1];
-      d[i * TX] = acc;
-    }
+    for (int k = WN - 2; k >= 0; --k) ring[k] += ring[k + 1];
   }
+  return s;
 }
 
 // Warp of the source image by the pair field (Sec. 2.1): M(p) = I(p + U(p)),
@@ -1605,83 +1579,139 @@ __global__ __launch_bounds__(BLOCK) void k_warp(const SimItem* __restrict__ item
     if (vs.ok[j]) sto(M, vs.p[j], tri_val(v[j], az[j].t, ay[j].t, ax[j].t));
 }
 
+// Statistics of the windows (Sec. 2.6): LNCC / SiLNCC per window, the loss, and
+// the adjoint's coefficients alpha, beta, gamma per window centre (0 where the
+// window leaves the volume).  The images are shifted by one value per chunk of
+// z before the products, which keeps the variance differences well conditioned.
+//
+// Where the images are flat those differences keep few digits, so the order of
+// every sum is part of the result.  It is: per patch column, running sums over
+// z of f, m, f^2, m^2 and f m, formed anew from the last w slices at the first
+// window of a chunk and every w-th after; then sums over x and over y in
+// segments of 8 that slide from the segment's start.  A block may take a part
+// of a chunk: parts are multiples of w windows, so each starts where the sums
+// are formed anew and the same values come out however the chunk is cut.
+//
+// Bound by vector issue and by the barriers of a slice.  The places of a
+// thread's segments are worked out once, waves without a second patch column
+// skip it, and the finished sums take the z-sums' LDS: three blocks of 16 x 32
+// columns share a CU.  12 pairs of 160x192x160 at w 7: 600 -> 417 us.
+template <int R, int TY, int TX>
+struct Box {
+  static constexpr int NT = TY * TX, WN = 2 * R + 1;
+  static constexpr int PY = TY + 2 * R, PX = TX + 2 * R, P1 = PY * PX;
+  static constexpr int NS = (P1 + NT - 1) / NT;   // patch columns per thread
+  static constexpr int PXS = PX | 1, TXS = TX + 1;  // odd: a wave's rows fall in distinct banks
+  static constexpr int SEG = 8, NXS = TX / SEG, NYS = TY / SEG;
+  static constexpr int ZQ = PY * PXS, XQ = PY * TXS, YQ = TY * TX;
+  static constexpr int XT = 5 * PY * NXS, XI = (XT + NT - 1) / NT;  // x tasks, and rounds of them
+  static constexpr int YT = 5 * TX * NYS;
+  static_assert(TX % SEG == 0 && TY % SEG == 0 && YT <= NT, "tile not a multiple of the segments");
+};
+
 template <int R, int TY, int TX>
 __global__ __launch_bounds__(TY * TX) void k_sim_stats(const SimItem* __restrict__ items, int n_items,
                                                        int n_tiles, int metric) {
-  using B = Box<R, TY, TX, 5>;
+  using B = Box<R, TY, TX>;
   constexpr int WN = B::WN, PX = B::PX, P1 = B::P1, NS = B::NS, NT = B::NT;
-  __shared__ float lds[B::LDS];
+  __shared__ float zs[5 * (B::ZQ > B::YQ ? B::ZQ : B::YQ)];  // z-sums; then the finished sums
+  __shared__ float xs[5 * B::XQ];
   __shared__ double red[NT / 64];
-  float* zs = lds;
-  float* xs = lds + 5 * B::ZQ;
-  float* ys = xs + 5 * B::XQ;
   const int tile = xcd_remap(blockIdx.x, n_tiles);
   const SimItem it = items[find_item(items, n_items, tile)];
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
-  const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, it.zc);
+  // the block's columns, its chunk [c0, c1) and its part [z0, z1) of it
+  const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, 1);
+  const int parts = (it.zc + it.zs - 1) / it.zs;
+  const int chunk = tc.z0 / parts;
+  const int c0 = chunk * it.zc, c1 = min(c0 + it.zc, D);
+  const int z0 = c0 + (tc.z0 - chunk * parts) * it.zs, z1 = min(z0 + it.zs, c1);
+  if (z0 >= z1) return;
   const cgfloat* __restrict__ F = gp(it.F);
   const cgfloat* __restrict__ M = gp(it.M);
-  gfloat* __restrict__ coef = gp(it.coef);
-  const int pm = (min((tc.z0 + tc.z1) / 2, D - 1) * H + min(tc.y0 + TY / 2, H - 1)) * W +
+  const Planes<gfloat> cf(gp(it.coef), V);
+  const bool coef = it.coef != nullptr;
+  const int pm = (min((c0 + c1) / 2, D - 1) * H + min(tc.y0 + TY / 2, H - 1)) * W +
                  min(tc.x0 + TX / 2, W - 1);
   const float sF = F[pm], sM = M[pm];
   const float inv_n = 1.f / (float)(WN * WN * WN);
-  const int ty = threadIdx.x / TX, tx = threadIdx.x % TX;
+  const int tid = threadIdx.x, ty = tid / TX, tx = tid % TX;
   const int y = tc.y0 + ty, x = tc.x0 + tx;
   const bool yx_in = (y < H) && (x < W);
   const bool yx_valid = yx_in && y >= R && y <= H - 1 - R && x >= R && x <= W - 1 - R;
-  // owned patch columns: offset in a slice (-1 outside the volume) and place
-  // in the z-sum rows
-  int cofs[NS], zofs[NS];
-  bool cval[NS];
+  // owned patch columns: offset in a slice and place in the z-sum rows.  A
+  // wave none of whose threads has a k-th column skips it.
+  uint32_t cofs[NS];
+  int zofs[NS];
+  bool cval[NS], cin[NS];
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
-    const int col = threadIdx.x + k * NT;
+    const int col = tid + k * NT;
     const int row = col / PX, cx = col % PX;
     const int yy = tc.y0 - R + row, xx = tc.x0 - R + cx;
     cval[k] = col < P1;
-    cofs[k] = (cval[k] && yy >= 0 && yy < H && xx >= 0 && xx < W) ? yy * W + xx : -1;
+    cin[k] = cval[k] && yy >= 0 && yy < H && xx >= 0 && xx < W;
+    cofs[k] = cin[k] ? (uint32_t)(yy * W + xx) : 0u;
     zofs[k] = row * B::PXS + cx;
   }
-  // shifted values of slice z at the owned columns (0 outside the volume)
-  auto load = [&](int z, float (&f)[NS], float (&m)[NS]) {
-    const bool zin = z >= 0 && z < D;
+  // values of slice z at the owned columns
+  float fn[NS], mn[NS];
+  auto load = [&](int z) {
+    const uint32_t base = (uint32_t)(min(max(z, 0), D - 1) * HW);
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-      const bool in = zin && cofs[k] >= 0;
-      const int p = in ? z * HW + cofs[k] : 0;
-      f[k] = in ? ldo(F, p) - sF : 0.f;
-      m[k] = in ? ldo(M, p) - sM : 0.f;
+      if (!cval[k]) continue;
+      fn[k] = ldo(F, base + cofs[k]);
+      mn[k] = ldo(M, base + cofs[k]);
     }
   };
-  // the last WN slices of each owned column (oldest first) and their sums
-  // of f, m, f^2, m^2 and f m over z; the sums are formed anew from the
-  // ring every WN slices, so rounding does not build up along the chunk
+  // this thread's segments of the x and y sums
+  int xsrc[B::XI], xdst[B::XI];
+  bool xon[B::XI];
+#pragma unroll
+  for (int i = 0; i < B::XI; ++i) {
+    const int e = tid + i * NT;
+    const int q = e / (B::PY * B::NXS), r = e - q * (B::PY * B::NXS);
+    const int row = r / B::NXS, seg = r - row * B::NXS;
+    xon[i] = e < B::XT;
+    xsrc[i] = q * B::ZQ + row * B::PXS + seg * B::SEG;
+    xdst[i] = q * B::XQ + row * B::TXS + seg * B::SEG;
+  }
+  const bool yon = tid < B::YT;
+  int ysrc, ydst;
+  {
+    const int q = tid / (TX * B::NYS), r = tid - q * (TX * B::NYS);
+    const int seg = r / TX, sx = r - seg * TX;
+    ysrc = q * B::XQ + seg * B::SEG * B::TXS + sx;
+    ydst = q * B::YQ + seg * B::SEG * TX + sx;
+  }
   float rf[NS][WN], rm[NS][WN], S[NS][5];
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
+    fn[k] = mn[k] = 0.f;
 #pragma unroll
     for (int j = 0; j < WN; ++j) rf[k][j] = rm[k][j] = 0.f;
 #pragma unroll
     for (int q = 0; q < 5; ++q) S[k][q] = 0.f;
   }
-  // values of slice zi are loaded one iteration ahead
-  float fn[NS], mn[NS];
-  load(tc.z0 - R, fn, mn);
+  load(z0 - R);
   int phase = 0;
   double lsum = 0.0;
-  for (int zi = tc.z0 - R; zi < tc.z1 + R; ++zi) {
+  for (int zi = z0 - R; zi < z1 + R; ++zi) {
     const bool exact = ++phase == WN;
     if (exact) phase = 0;
+    const bool zin = zi >= 0 && zi < D;
     float fv[NS], mv[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-      fv[k] = fn[k];
-      mv[k] = mn[k];
+      const bool in = zin && cin[k];
+      fv[k] = in ? fn[k] - sF : 0.f;
+      mv[k] = in ? mn[k] - sM : 0.f;
     }
-    load(zi + 1, fn, mn);
+    load(zi + 1);
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
+      if (!cval[k]) continue;
       const float fo = rf[k][0], mo = rm[k][0];
 #pragma unroll
       for (int j = 0; j + 1 < WN; ++j) {
@@ -1711,70 +1741,82 @@ __global__ __launch_bounds__(TY * TX) void k_sim_stats(const SimItem* __restrict
       }
     }
     const int zcen = zi - R;
-    if (zcen >= tc.z0) {
-      const bool zvalid = zcen >= R && zcen <= D - 1 - R;
-      if (zvalid) {
+    if (zcen < z0) continue;
+    const bool zvalid = zcen >= R && zcen <= D - 1 - R;
+    if (zvalid) {
 #pragma unroll
-        for (int k = 0; k < NS; ++k) {
-          if (!cval[k]) continue;
+      for (int k = 0; k < NS; ++k) {
+        if (!cval[k]) continue;
 #pragma unroll
-          for (int q = 0; q < 5; ++q) zs[q * B::ZQ + zofs[k]] = S[k][q];
-        }
-        __syncthreads();
-        box_x<B>(zs, xs, 5);
-        __syncthreads();
-        box_y<B>(xs, ys, 5);
-        __syncthreads();
+        for (int q = 0; q < 5; ++q) zs[q * B::ZQ + zofs[k]] = S[k][q];
       }
-      if (yx_in) {
-        const int p = (zcen * H + y) * W + x;
-        float al = 0.f, be = 0.f, ga = 0.f;
-        if (zvalid && yx_valid) {
-          float Sw[5];
+      __syncthreads();
 #pragma unroll
-          for (int q = 0; q < 5; ++q) Sw[q] = ys[q * B::YQ + threadIdx.x];
-          const float mF = Sw[0] * inv_n, mM = Sw[1] * inv_n;
-          const float vFr = Sw[2] * inv_n - mF * mF;
-          const float vMr = Sw[3] * inv_n - mM * mM;
-          const float c = Sw[4] * inv_n - mF * mM;
-          const float vF = fmaxf(vFr, 0.f), vM = fmaxf(vMr, 0.f);
-          float l, av, ac;
-          if (metric == 0) {
-            const float den = vF * vM;
-            if (den > EPS_LNCC) {
-              const float sd = sqrtf(den);
-              l = 1.f - c / sd;
-              ac = -1.f / sd;
-              av = c / (2.f * vM * sd);
-            } else {
-              const float sd = sqrtf(EPS_LNCC);
-              l = 1.f - c / sd;
-              ac = -1.f / sd;
-              av = 0.f;
-            }
+      for (int i = 0; i < B::XI; ++i) {
+        if (!xon[i]) continue;
+        float v[7 + WN];
+#pragma unroll
+        for (int k = 0; k < 7 + WN; ++k) v[k] = zs[xsrc[i] + k];
+        slide8<WN, 1>(v, xs + xdst[i]);
+      }
+      __syncthreads();
+      if (yon) {
+        float v[7 + WN];
+#pragma unroll
+        for (int k = 0; k < 7 + WN; ++k) v[k] = xs[ysrc + k * B::TXS];
+        slide8<WN, TX>(v, zs + ydst);
+      }
+      __syncthreads();
+    }
+    if (yx_in) {
+      float al = 0.f, be = 0.f, ga = 0.f;
+      if (zvalid && yx_valid) {
+        float Sw[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) Sw[q] = zs[q * B::YQ + tid];
+        const float mF = Sw[0] * inv_n, mM = Sw[1] * inv_n;
+        const float vFr = Sw[2] * inv_n - mF * mF;
+        const float vMr = Sw[3] * inv_n - mM * mM;
+        const float c = Sw[4] * inv_n - mF * mM;
+        const float vF = fmaxf(vFr, 0.f), vM = fmaxf(vMr, 0.f);
+        float l, av, ac;
+        if (metric == 0) {
+          const float den = vF * vM;
+          if (den > EPS_LNCC) {
+            const float sd = sqrtf(den);
+            l = 1.f - c / sd;
+            ac = -1.f / sd;
+            av = c / (2.f * vM * sd);
           } else {
-            const float dd = fmaxf(vF, EPS_SILNCC);
-            l = vM - c * c / dd;
-            ac = -2.f * c / dd;
-            av = 1.f;
+            const float sd = sqrtf(EPS_LNCC);
+            l = 1.f - c / sd;
+            ac = -1.f / sd;
+            av = 0.f;
           }
-          if (!(vMr > 0.f)) av = 0.f;
-          lsum += (double)l;
-          const float mFt = mF + sF, mMt = mM + sM;
-          al = -(2.f * mMt * av + mFt * ac) * inv_n;
-          be = av * inv_n;
-          ga = ac * inv_n;
+        } else {
+          const float dd = fmaxf(vF, EPS_SILNCC);
+          l = vM - c * c / dd;
+          ac = -2.f * c / dd;
+          av = 1.f;
         }
-        if (coef) {
-          sto(coef, p, al);
-          sto(coef + V, p, be);
-          sto(coef + 2 * V, p, ga);
-        }
+        if (!(vMr > 0.f)) av = 0.f;
+        lsum += (double)l;
+        const float mFt = mF + sF, mMt = mM + sM;
+        al = -(2.f * mMt * av + mFt * ac) * inv_n;
+        be = av * inv_n;
+        ga = ac * inv_n;
+      }
+      if (coef) {
+        const uint32_t p = (uint32_t)((zcen * H + y) * W + x);
+        sto(cf.c[0], p, al);
+        sto(cf.c[1], p, be);
+        sto(cf.c[2], p, ga);
       }
     }
+    if (zvalid) __syncthreads();  // zs is written again next
   }
   const double tot = block_sum<NT>(lsum, red);
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     const double v = tot * it.inv_nr;
     if (it.js) unsafeAtomicAdd(&it.js->loss_sim, v);
     if (it.sim_out) unsafeAtomicAdd(it.sim_out, v);
@@ -1784,54 +1826,70 @@ __global__ __launch_bounds__(TY * TX) void k_sim_stats(const SimItem* __restrict
 // Gradient of Sim with respect to the pair field:
 //   dSim/dM(y) = (Box alpha + 2 M Box beta + F Box gamma)(y) / N_R,
 //   dSim/dU(y) = dSim/dM(y) * grad I_j(y + U(y)).
-// The window sums of the coefficients are formed like those of k_sim_stats;
-// the coefficients of the next slice and the output voxel's loads are issued
-// before the current slice's sums.
+// The window sums of the coefficients are formed like those of k_sim_stats.
+// The field at an output voxel is loaded two slices ahead of its use, the
+// corners of the cell it samples one slice ahead.
 template <int R, int TY, int TX>
 __global__ __launch_bounds__(TY * TX) void k_sim_grad(const SimItem* __restrict__ items, int n_items,
                                                       int n_tiles) {
-  using B = Box<R, TY, TX, 3>;
-  constexpr int WN = B::WN, PX = B::PX, P1 = B::P1, NS = B::NS, NT = B::NT;
-  __shared__ float lds[B::LDS];
-  float* zs = lds;
-  float* xs = lds + 3 * B::ZQ;
-  float* ys = xs + 3 * B::XQ;
+  using B = Win<R, TY, TX>;
+  constexpr int NT = B::NT, NS = B::NS, WN = B::WN, XT = B::XT, XQ = B::XQ;
+  static_assert(3 * XT <= NT, "one x-sum task per thread");
+  __shared__ float raw[2][3][B::SLICE];
+  __shared__ float xs[2][3 * XQ];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
   const SimItem it = items[find_item(items, n_items, tile)];
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
-  const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, it.zc);
+  const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, it.zg);
   const cgfloat* __restrict__ F = gp(it.F);
   const cgfloat* __restrict__ I = gp(it.I);
-  const cgfloat* __restrict__ U = gp(it.U);
-  const cgfloat* __restrict__ coef = gp(it.coef);
-  gfloat* __restrict__ gU = gp(it.gU);
+  const Planes<const cgfloat> Up(gp(it.U), V), cf(gp((const float*)it.coef), V);
+  const Planes<gfloat> gU(gp(it.gU), V);
   const float inv_nr = (float)it.inv_nr;
-  const int ty = threadIdx.x / TX, tx = threadIdx.x % TX;
-  const int y = tc.y0 + ty, x = tc.x0 + tx;
-  const bool yx_in = y < H && x < W;
-  int cyy[NS], cxx[NS], zofs[NS];
-  bool cin[NS], cval[NS];
+  const int tid = threadIdx.x, ty = tid / TX, tx = tid % TX;
+  const int y = min(tc.y0 + ty, H - 1), x = min(tc.x0 + tx, W - 1);
+  const bool yx_in = tc.y0 + ty < H && tc.x0 + tx < W;
+  const uint32_t off = (uint32_t)(y * W + x);
+  uint32_t soff[NS];
+  bool sin[NS];
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
-    const int col = threadIdx.x + k * NT;
-    const int row = col / PX, cx = col % PX;
-    cval[k] = col < P1;
-    cyy[k] = tc.y0 - R + row;
-    cxx[k] = tc.x0 - R + cx;
-    zofs[k] = row * B::PXS + cx;
-    cin[k] = cval[k] && cyy[k] >= 0 && cyy[k] < H && cxx[k] >= 0 && cxx[k] < W;
+    const int i = tid + k * NT, row = i / B::PXS, col = i - row * B::PXS;
+    const int yy = tc.y0 - R + row, xx = tc.x0 - R + col;
+    sin[k] = yy >= 0 && yy < H && xx >= 0 && xx < W;
+    soff[k] = sin[k] ? (uint32_t)(yy * W + xx) : 0u;
   }
-  auto load_coef = [&](int z, float (&c)[NS][3]) {
+  float cv[3][NS];  // coefficients off the grid are 0
+#pragma unroll
+  for (int k = 0; k < NS; ++k) cv[0][k] = cv[1][k] = cv[2][k] = 0.f;
+  auto load = [&](int z) {
+    const uint32_t base = (uint32_t)(min(max(z, 0), D - 1) * HW);
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-      const bool in = cin[k] && z >= 0 && z < D;
-      const int p = in ? (z * H + cyy[k]) * W + cxx[k] : 0;
-      c[k][0] = in ? coef[p] : 0.f;
-      c[k][1] = in ? coef[V + p] : 0.f;
-      c[k][2] = in ? coef[2 * V + p] : 0.f;
+      if (!sin[k]) continue;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) cv[q][k] = ldo(cf.c[q], base + soff[k]);
     }
   };
-  // output voxel (zo, y, x): U first, then F and the corners of I
+  auto put = [&](int b) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int k = 0; k < NS; ++k) raw[b][q][tid + k * NT] = cv[q][k];
+  };
+  const bool xt = tid < 3 * XT;
+  const int xq = xt ? tid / XT : 0, xr = xt ? tid - xq * XT : 0;
+  const int xrow = xr / B::NSEG, xseg = (xr - xrow * B::NSEG) * B::SEG;
+  const int xsrc = xq * B::SLICE + xrow * B::PXS + xseg,
+            xdst = xq * XQ + xrow * B::TXS + xseg;
+  auto sum_x = [&](int b) {
+    if (!xt) return;
+    const float* s = &raw[b][0][0] + xsrc;
+    float v[7 + WN];
+#pragma unroll
+    for (int k = 0; k < 7 + WN; ++k) v[k] = s[k];
+    slide8<WN, 1>(v, xs[b] + xdst);
+  };
   float rA[9], rO[3];
   const bool rigid = it.rigid != nullptr;
   if (rigid) {
@@ -1840,107 +1898,81 @@ __global__ __launch_bounds__(TY * TX) void k_sim_grad(const SimItem* __restrict_
 #pragma unroll
     for (int k = 0; k < 3; ++k) rO[k] = it.rigid->off[k];
   }
-  auto load_uo = [&](int zo, float (&u)[3]) {
-    const bool in = yx_in && zo >= 0 && zo < D;
-    const int p = in ? (zo * H + y) * W + x : 0;
-    u[0] = in ? U[p] : 0.f;
-    u[1] = in ? U[V + p] : 0.f;
-    u[2] = in ? U[2 * V + p] : 0.f;
-    if (rigid && in) {
-      const float fz = (float)zo, fy = (float)y, fx = (float)x;
+  float u[3];  // U at the own column, of the output after next's preparation
+  auto load_u = [&](int z) {
+    const uint32_t p = (uint32_t)(min(z, D - 1) * HW) + off;
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        u[c] += fmaf(rA[3 * c], fz, fmaf(rA[3 * c + 1], fy, fmaf(rA[3 * c + 2], fx, rO[c])));
-    }
+    for (int c = 0; c < 3; ++c) u[c] = ldo(Up.c[c], p);
   };
-  float c0[NS][3];
-  load_coef(tc.z0 - R, c0);
-  float uo[3];
-  load_uo(tc.z0, uo);
-  // the last WN slices of the coefficients of each owned column and their
-  // sums over z (formed anew every WN slices)
-  float rc[NS][3][WN], S[NS][3];
+  const int zb = tc.z0 - R, total = tc.z1 - tc.z0 + 2 * R;
+  load(zb);
+  put(0);
+  load(zb + 1);
+  load_u(tc.z0);
+  __syncthreads();
+  sum_x(0);
+  put(1);
+  load(zb + 2);
+  __syncthreads();
+  float ring[3][WN], pre[3];
 #pragma unroll
-  for (int k = 0; k < NS; ++k)
+  for (int q = 0; q < 3; ++q) {
+    pre[q] = 0.f;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      S[k][q] = 0.f;
+    for (int k = 0; k < WN; ++k) ring[q][k] = 0.f;
+  }
+  float vI[8], fo = 0.f;   // corners of I and F of the next output
+  Ax az{}, ay{}, ax{};
 #pragma unroll
-      for (int j = 0; j < WN; ++j) rc[k][q][j] = 0.f;
-    }
-  int phase = 0;
-  for (int zi = tc.z0 - R; zi < tc.z1 + R; ++zi) {
-    const bool exact = ++phase == WN;
-    if (exact) phase = 0;
+  for (int k = 0; k < 8; ++k) vI[k] = 0.f;
+  bool more = true;
+  for (int n0 = 0; more; n0 += WN) {
 #pragma unroll
-    for (int k = 0; k < NS; ++k)
+    for (int j = 0; j < WN; ++j) {
+      const int n = n0 + j;
+      if (n >= total) {
+        more = false;
+        break;
+      }
+      const int zi = zb + n, zo = zi - R;
+      const bool zin = zi >= 0 && zi < D;  // slices off the grid hold zeros
+      put(n & 1);
+      load(zi + 3);
+      float S[3];
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        const float o = rc[k][q][0];
+        const float* s = xs[n & 1] + q * XQ + ty * B::TXS + tx;
+        float v = s[0];
 #pragma unroll
-        for (int j = 0; j + 1 < WN; ++j) rc[k][q][j] = rc[k][q][j + 1];
-        rc[k][q][WN - 1] = c0[k][q];
-        if (exact) {
-          float s = 0.f;
-#pragma unroll
-          for (int j = 0; j < WN; ++j) s += rc[k][q][j];
-          S[k][q] = s;
-        } else {
-          S[k][q] += c0[k][q] - o;
-        }
+        for (int k = 1; k < WN; ++k) v += s[k * B::TXS];
+        S[q] = window_sum<WN>(ring[q], pre[q], j, zin ? v : 0.f);
       }
-    float c1[NS][3];
-    load_coef(zi + 1, c1);
-    const int zo = zi - R;
-    const bool out_now = zo >= tc.z0;
-    // loads of the output voxel of this iteration
-    float vI[8], fo = 0.f;
-    Ax az, ay, ax;
-    {
-      const bool in = yx_in && zo >= tc.z0 && zo < D;
-      const int zz = in ? zo : 0, yy = in ? y : 0, xx = in ? x : 0;
-      az = axis_disp(zz, uo[0], D);
-      ay = axis_disp(yy, uo[1], H);
-      ax = axis_disp(xx, uo[2], W);
-      load8(I, (az.i0 * H + ay.i0) * W + ax.i0, W, HW, vI);
-      fo = F[(zz * H + yy) * W + xx];
-    }
-    float un[3];
-    load_uo(out_now ? zo + 1 : tc.z0, un);
-    if (out_now) {
-#pragma unroll
-      for (int k = 0; k < NS; ++k) {
-        if (!cval[k]) continue;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) zs[q * B::ZQ + zofs[k]] = S[k][q];
-      }
-      __syncthreads();
-      box_x<B>(zs, xs, 3);
-      __syncthreads();
-      box_y<B>(xs, ys, 3);
-      __syncthreads();
-      if (yx_in) {
-        const float B0 = ys[threadIdx.x], B1 = ys[B::YQ + threadIdx.x],
-                    B2 = ys[2 * B::YQ + threadIdx.x];
-        const int p = (zo * H + y) * W + x;
+      if (zo >= tc.z0 && yx_in) {
         float dz, dy, dx;
         const float M = tri_grad(vI, az.t, ay.t, ax.t, dz, dy, dx);
-        const float dM = (B0 + 2.f * M * B1 + fo * B2) * inv_nr;
-        gU[p] = dM * dz * az.live;
-        gU[V + p] = dM * dy * ay.live;
-        gU[2 * V + p] = dM * dx * ax.live;
+        const float dM = (S[0] + 2.f * M * S[1] + fo * S[2]) * inv_nr;
+        const uint32_t p = (uint32_t)(zo * HW) + off;
+        sto(gU.c[0], p, dM * dz * az.live);
+        sto(gU.c[1], p, dM * dy * ay.live);
+        sto(gU.c[2], p, dM * dx * ax.live);
       }
-    }
+      if (zo + 1 >= tc.z0 && zo + 1 < tc.z1) {
+        const int zn = zo + 1;
+        if (rigid) {
+          const float fz = (float)zn, fy = (float)y, fx = (float)x;
 #pragma unroll
-    for (int k = 0; k < NS; ++k) {
-      c0[k][0] = c1[k][0];
-      c0[k][1] = c1[k][1];
-      c0[k][2] = c1[k][2];
-    }
-    if (out_now) {
-      uo[0] = un[0];
-      uo[1] = un[1];
-      uo[2] = un[2];
+          for (int c = 0; c < 3; ++c)
+            u[c] += fmaf(rA[3 * c], fz, fmaf(rA[3 * c + 1], fy, fmaf(rA[3 * c + 2], fx, rO[c])));
+        }
+        az = axis_disp(zn, u[0], D);
+        ay = axis_disp(y, u[1], H);
+        ax = axis_disp(x, u[2], W);
+        load8(I, (az.i0 * H + ay.i0) * W + ax.i0, W, HW, vI);
+        fo = ldo(F, (uint32_t)(zn * HW) + off);
+        load_u(zn + 1);
+      }
+      sum_x((n + 1) & 1);
+      __syncthreads();
     }
   }
 }

@@ -179,8 +179,10 @@ __host__ __device__ inline void rigid_rotation(const float th[3], int deriv, flo
 struct SimItem {
   int tile0;
   int D, H, W;
-  int zc;        // z-chunk length of this item's tiles
-  int pad;
+  int zc;        // z-chunk length of the tiling: the statistics' sums are formed per chunk
+  int zs;        // windows along z that a block of the statistics walks: zc, or less, then a
+                 // multiple of the window
+  int zg;        // planes that a block of the gradient walks
   const float* F;
   const float* I;
   const float* U;
@@ -327,6 +329,10 @@ constexpr int CT_Z = 8, CT_Y = 8, CT_X = 32;
 constexpr int SIM_SHAPES = 3;
 constexpr int SIM_SHAPE_Y[SIM_SHAPES] = {8, 16, 8};
 constexpr int SIM_SHAPE_X[SIM_SHAPES] = {32, 32, 64};
+// Blocks of each shape of the statistics and of the gradient that run at once
+// (by their registers: 74 to 102 and 93 to 97 at w 7).
+constexpr int STAT_SLOTS[SIM_SHAPES] = {1024, 768, 512};
+constexpr int GRAD_SLOTS[SIM_SHAPES] = {1024, 512, 512};
 constexpr int ELEM_PER_BLOCK = 1024;           // elementwise kernels
 
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -339,8 +345,14 @@ inline int march_tiles(int D, int H, int W, int zc) {
 inline int combine_tiles(int D, int H, int W) {
   return ceil_div(D, CT_Z) * ceil_div(H, CT_Y) * ceil_div(W, CT_X);
 }
-inline int stat_tiles(int D, int H, int W, int zc, int shape) {
-  return ceil_div(D, zc) * ceil_div(H, SIM_SHAPE_Y[shape]) * ceil_div(W, SIM_SHAPE_X[shape]);
+inline int sim_cols(int H, int W, int shape) {
+  return ceil_div(H, SIM_SHAPE_Y[shape]) * ceil_div(W, SIM_SHAPE_X[shape]);
+}
+inline int stat_tiles(int D, int H, int W, int zc, int zs, int shape) {
+  return ceil_div(D, zc) * ceil_div(zc, zs) * sim_cols(H, W, shape);
+}
+inline int grad_tiles(int D, int H, int W, int zg, int shape) {
+  return ceil_div(D, zg) * sim_cols(H, W, shape);
 }
 
 // Launchers (kernels.hip).  All return hipError_t of the launch.

@@ -904,8 +904,55 @@ void add_rigid_stages(Builder& b, const std::vector<Job*>& jobs) {
   b.add(ST_RIGID_STEP, si, (int)si.size(), 0.0);
 }
 
+// How the pairs of a launch are cut along z.  A block walks z + w - 1 slices
+// and a fixed number of blocks walk at once: of the cuts on offer the one that
+// ends first.  The statistics take the chunks of the tiling or parts of them, the
+// gradient any number of planes, both in multiples of the window, which leaves
+// every sum as it is.  One pair of 32^3 at w 5 under a chunk of 32: statistics
+// 48 -> 12 us in parts of 5, gradient 33 -> 9; six pairs of 64^3 at w 7: 60 ->
+// 40 and 75 -> 32 us.
+void set_sim_parts(std::vector<SimItem>& items, int window, int shape) {
+  auto cost = [&](double blocks, int slots, int z) {
+    const double rounds = blocks / slots;
+    // few rounds end together; over many, blocks start as others end
+    return (rounds < 4.0 ? std::ceil(rounds) : rounds) * (z + window - 1);
+  };
+  auto stat_blocks = [&](int z) {  // parts of z windows; 0: whole chunks
+    double n = 0;
+    for (const SimItem& it : items)
+      n += stat_tiles(it.D, it.H, it.W, it.zc, z ? std::min(z, it.zc) : it.zc, shape);
+    return n;
+  };
+  auto grad_blocks = [&](int z) {
+    double n = 0;
+    for (const SimItem& it : items) n += grad_tiles(it.D, it.H, it.W, z, shape);
+    return n;
+  };
+  int zmax = 1, zs = 0, zg = window;
+  for (const SimItem& it : items) zmax = std::max(zmax, it.zc);
+  const int ss = STAT_SLOTS[shape], gs = GRAD_SLOTS[shape];
+  double best = cost(stat_blocks(0), ss, zmax), best_g = 1e300;
+  for (int z = window; z < 64 + window; z += window) {
+    const double c = z < zmax ? cost(stat_blocks(z), ss, z) : best;
+    if (c < best) {
+      best = c;
+      zs = z;
+    }
+    const double g = cost(grad_blocks(z), gs, z);
+    if (g < best_g) {
+      best_g = g;
+      zg = z;
+    }
+  }
+  for (SimItem& it : items) {
+    it.zs = zs ? std::min(zs, it.zc) : it.zc;
+    it.zg = zg;
+  }
+}
+
 // The pair items of the jobs whose window statistics use tile shape `shape`.
-std::vector<SimItem> sim_items(const std::vector<Job*>& jobs, int shape, int& tiles, double& vox) {
+std::vector<SimItem> sim_items(const std::vector<Job*>& jobs, int shape, bool grad, int& tiles,
+                               double& vox) {
   std::vector<SimItem> items;
   tiles = 0;
   vox = 0;
@@ -920,7 +967,6 @@ std::vector<SimItem> sim_items(const std::vector<Job*>& jobs, int shape, int& ti
       for (int j = 0; j < N; ++j) {
         if (i == j) continue;
         SimItem it{};
-        it.tile0 = tiles;
         it.D = d[0]; it.H = d[1]; it.W = d[2];
         it.zc = tl.zc;
         it.F = J->image(i);
@@ -934,9 +980,14 @@ std::vector<SimItem> sim_items(const std::vector<Job*>& jobs, int shape, int& ti
         it.sim_out = nullptr;
         it.rigid = (J->p.rigid && j >= 1) ? J->rigid(j) : nullptr;
         items.push_back(it);
-        tiles += stat_tiles(d[0], d[1], d[2], tl.zc, shape);
         vox += (double)J->VIc();
       }
+  }
+  set_sim_parts(items, jobs[0]->p.window, shape);
+  for (SimItem& it : items) {
+    it.tile0 = tiles;
+    tiles += grad ? grad_tiles(it.D, it.H, it.W, it.zg, shape)
+                  : stat_tiles(it.D, it.H, it.W, it.zc, it.zs, shape);
   }
   return items;
 }
@@ -952,7 +1003,7 @@ void add_sim_stages(Builder& b, const std::vector<Job*>& jobs, StageKind kind) {
     for (int shape = 0; shape < SIM_SHAPES; ++shape) {
       int t;
       double v;
-      for (SimItem it : sim_items(jobs, shape, t, v)) {
+      for (SimItem it : sim_items(jobs, shape, false, t, v)) {
         it.tile0 = tiles;
         tiles += point_tiles(it.D, it.H, it.W);
         vox += (double)it.D * it.H * it.W;
@@ -964,7 +1015,7 @@ void add_sim_stages(Builder& b, const std::vector<Job*>& jobs, StageKind kind) {
   for (int shape = 0; shape < SIM_SHAPES; ++shape) {
     int tiles;
     double vox;
-    auto items = sim_items(jobs, shape, tiles, vox);
+    auto items = sim_items(jobs, shape, kind == ST_SIM_GRAD, tiles, vox);
     if (items.empty()) continue;
     const double per = kind == ST_SIM_STATS ? B_SIM_STATS : B_SIM_GRAD;
     b.add(kind, items, tiles, per * vox, window, kind == ST_SIM_STATS ? metric : 0);
@@ -1687,9 +1738,9 @@ SimTile tune_sim_tile(Ctx* ctx, const int dims[3], int window, int metric, hipSt
   float best_ms = 1e30f;
   for (int shape = 0; shape < SIM_SHAPES; ++shape)
     for (int zc : zcs) {
-      const int per = stat_tiles(dims[0], dims[1], dims[2], zc, shape);
+      const int per = stat_tiles(dims[0], dims[1], dims[2], zc, zc, shape);
       for (int k = 0; k < P; ++k) {
-        its[k].zc = zc;
+        its[k].zc = its[k].zs = its[k].zg = zc;  // what is timed is this cut
         its[k].tile0 = k * per;
       }
       MUSTER_HIP(hipMemcpyAsync(item.p, its.data(), (size_t)P * sizeof(SimItem),
@@ -2285,9 +2336,12 @@ muster_status muster_sim(muster_ctx* h, void* stream, const int dims[3], int win
     warped.alloc(ctx, V * sizeof(float));
     const int r = (window - 1) / 2;
     const SimTile tl = choose_sim_tile(ctx, dims, window, metric, sc.s);
-    SimItem it{};
+    std::vector<SimItem> one(1);
+    SimItem& it = one[0];
+    it = SimItem{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.zc = tl.zc;
+    set_sim_parts(one, window, tl.shape);
     it.F = F;
     it.I = I;
     it.U = U;
@@ -2302,11 +2356,12 @@ muster_status muster_sim(muster_ctx* h, void* stream, const int dims[3], int win
     MUSTER_HIP(hipMemsetAsync(ctx->step_acc, 0, sizeof(double), sc.s));
     MUSTER_HIP(launch_warp((const SimItem*)(sc.dev() + off), 1,
                            point_tiles(dims[0], dims[1], dims[2]), sc.s));
-    const int tiles = stat_tiles(dims[0], dims[1], dims[2], tl.zc, tl.shape);
+    const int tiles = stat_tiles(it.D, it.H, it.W, it.zc, it.zs, tl.shape),
+              gtiles = grad_tiles(it.D, it.H, it.W, it.zg, tl.shape);
     MUSTER_HIP(launch_sim_stats((const SimItem*)(sc.dev() + off), 1, tiles, window, metric,
                                 tl.shape, sc.s));
     if (grad_U)
-      MUSTER_HIP(launch_sim_grad((const SimItem*)(sc.dev() + off), 1, tiles, window, tl.shape,
+      MUSTER_HIP(launch_sim_grad((const SimItem*)(sc.dev() + off), 1, gtiles, window, tl.shape,
                                  sc.s));
     MUSTER_HIP(hipMemcpyAsync(sim_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, sc.s));
     MUSTER_HIP(hipStreamSynchronize(sc.s));
@@ -2349,9 +2404,12 @@ muster_status muster_sim_noalloc(muster_ctx* h, void* stream, const int dims[3],
       if (f != ctx->tuned.end()) tl = f->second;
     }
     const int r = (window - 1) / 2;
-    SimItem it{};
+    std::vector<SimItem> one(1);
+    SimItem& it = one[0];
+    it = SimItem{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.zc = tl.zc;
+    set_sim_parts(one, window, tl.shape);
     it.F = F;
     it.I = I;
     it.U = U;
@@ -2367,11 +2425,12 @@ muster_status muster_sim_noalloc(muster_ctx* h, void* stream, const int dims[3],
     MUSTER_HIP(launch_fill(reinterpret_cast<float*>(sum), 2, 0.f, sc.s));
     MUSTER_HIP(launch_warp((const SimItem*)(sc.dev() + off), 1,
                            point_tiles(dims[0], dims[1], dims[2]), sc.s));
-    const int tiles = stat_tiles(dims[0], dims[1], dims[2], tl.zc, tl.shape);
+    const int tiles = stat_tiles(it.D, it.H, it.W, it.zc, it.zs, tl.shape),
+              gtiles = grad_tiles(it.D, it.H, it.W, it.zg, tl.shape);
     MUSTER_HIP(launch_sim_stats((const SimItem*)(sc.dev() + off), 1, tiles, window, metric,
                                 tl.shape, sc.s));
     if (grad_U)
-      MUSTER_HIP(launch_sim_grad((const SimItem*)(sc.dev() + off), 1, tiles, window, tl.shape,
+      MUSTER_HIP(launch_sim_grad((const SimItem*)(sc.dev() + off), 1, gtiles, window, tl.shape,
                                  sc.s));
     MUSTER_HIP(hipMemcpyAsync(sim_host, sum, sizeof(double), hipMemcpyDeviceToHost, sc.s));
     MUSTER_HIP(hipStreamSynchronize(sc.s));
