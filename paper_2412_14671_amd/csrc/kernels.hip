@@ -1103,19 +1103,19 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const ExpBwdItem* __restrict_
 
 // What the voxels that are not near spread, added into the field that
 // k_exp_bwd has written, over the point tiles it marked.  A block looks at
-// FAR_GROUP marks with one load and ends there when none is set, which is
+// `group` marks with one load and ends there when none is set, which is
 // the usual case: displacements reach a voxel only in the last squarings of a
 // large deformation.  The marks are cleared once read.  DETMAX: the
 // deterministic mode's reduce-only pass (no writes but the job's slot).
 template <bool DETMAX>
-__global__ __launch_bounds__(BLOCK) void k_exp_far(const ExpBwdItem* __restrict__ items,
-                                                   int n_items, int n_tiles) {
+__global__ __launch_bounds__(BLOCK) void k_exp_far(const ExpBwdItem* __restrict__ items, int n_items,
+                                                   int n_tiles, int group) {
   __shared__ __align__(16) int acc[DETMAX ? 4 : 3 * SCATTER_CELLS];
   __shared__ int sred[8 * (BLOCK / 64)];
   const int lane = threadIdx.x & 63;
-  const int mine = blockIdx.x * FAR_GROUP + lane;
+  const int mine = blockIdx.x * group + lane;
   int mark = 0;
-  if (lane < FAR_GROUP && mine < n_tiles) {
+  if (lane < group && mine < n_tiles) {
     const ExpBwdItem& m = items[find_item(items, n_items, mine)];
     mark = m.far[mine - m.tile0];
   }
@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(BLOCK) void k_exp_far(const ExpBwdItem* __restrict_
   if (!todo) return;
   __syncthreads();  // every wave has read the marks
   while (todo) {
-    const int tile = blockIdx.x * FAR_GROUP + __builtin_ctzll(todo);
+    const int tile = blockIdx.x * group + __builtin_ctzll(todo);
     todo &= todo - 1;
     const ExpBwdItem it = items[find_item(items, n_items, tile)];
     const int D = it.D, H = it.H, W = it.W, V = D * H * W;
@@ -2412,17 +2412,24 @@ hipError_t launch_compose_fwd(const ComposeItem* items, int n_items, int n_tiles
   return hipGetLastError();
 }
 
+// Marks per block of k_exp_far: blocks that look at more end sooner where none
+// is set (28800 marks in eights: 6 us), but take their marked tiles one after
+// another.
+static int far_group(int n_tiles) { return n_tiles < 4096 ? 1 : n_tiles < 16384 ? 4 : 8; }
+
 hipError_t launch_exp_far_detmax(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_exp_far<true>, dim3(ceil_div(n_tiles, FAR_GROUP)), dim3(BLOCK), 0, s, items,
-                n_items, n_tiles);
+  const int group = far_group(n_tiles);
+  MUSTER_LAUNCH(k_exp_far<true>, dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items, n_items,
+                n_tiles, group);
   return hipGetLastError();
 }
 
 hipError_t launch_exp_far(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_exp_far<false>, dim3(ceil_div(n_tiles, FAR_GROUP)), dim3(BLOCK), 0, s, items,
-                n_items, n_tiles);
+  const int group = far_group(n_tiles);
+  MUSTER_LAUNCH(k_exp_far<false>, dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items, n_items,
+                n_tiles, group);
   return hipGetLastError();
 }
 

@@ -317,10 +317,11 @@ constexpr int PT_Z = 8, PT_Y = 8, PT_X = 16;   // 1024 voxels, 256 threads
 constexpr int PT_VOX = PT_Z * PT_Y * PT_X;
 constexpr int BLOCK = 256;
 constexpr int SCATTER_CELLS = 2048;          // LDS bins per component
-// Columns of a marching block (y, x), and the marks a block of k_exp_far reads.
+// Columns of a marching block (y, x).
 constexpr int MT_Y = 8, MT_X = 32;
-constexpr int FAR_GROUP = 8;
-constexpr int MARCH_BLOCKS = 1024;             // blocks that fill the chip
+// Blocks of the marching kernels that run at once: five and eight per CU (94
+// and 56 registers).
+constexpr int EXP_BWD_SLOTS = 1280, EXP_FWD_SLOTS = 2048;
 // Tiles of the combination of the SVF gradients.
 constexpr int CT_Z = 8, CT_Y = 8, CT_X = 32;
 // Tiles of the windowed-statistics kernels: TY x TX columns, z chunks.

@@ -179,8 +179,24 @@ void validate_problem(int N, const int dims[3], const muster_params& p, const do
   }
 }
 
+// Fields per direction that the footprint counts for the squaring steps.
 static int per_dir_fields(const muster_params& p) {
   return p.exp_mode == MUSTER_EXP_STORE ? p.K : 3;
+}
+
+// Fields per direction that a job holds: u_K and, in recompute mode, a ring of
+// the last REC_SLOTS steps before it (two more than the footprint names; they
+// fit the room it holds for the adjoint).
+static int ring_slots(int K) { return std::max(1, std::min(REC_SLOTS, K - 1)); }
+static int held_fields(const muster_params& p) {
+  return p.exp_mode == MUSTER_EXP_STORE ? p.K : 1 + ring_slots(p.K);
+}
+
+// Recompute mode: whether u_1..u_s are formed anew before the adjoint's step s.
+// The ring then holds the last steps up to s, so that happens once per turn of
+// the ring, and not before the first, whose steps the forward pass has left.
+static bool ring_refill(int K, int s) {
+  return s >= 1 && s < K - 1 && (K - 1 - s) % ring_slots(K) == 0;
 }
 
 uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
@@ -235,13 +251,13 @@ Job::~Job() {
 }
 
 float* Job::us_field(int dir, int slot) const {
-  return field(m_us.as<float>(), (size_t)dir * per_dir_fields(p) + slot);
+  return field(m_us.as<float>(), (size_t)dir * held_fields(p) + slot);
 }
 
 float* Job::u_step(int dir, int s) const {
   if (p.exp_mode == MUSTER_EXP_STORE) return us_field(dir, s - 1);
   if (s == p.K) return us_field(dir, 0);
-  return us_field(dir, 1 + ((s - 1) % 2));
+  return us_field(dir, 1 + (s - 1) % ring_slots(p.K));
 }
 
 float* Job::pair_field(int i, int j) const {
@@ -307,7 +323,7 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
   J.m_phi.alloc(ctx, n1 * F);
   J.m_m.alloc(ctx, n1 * F);
   J.m_v.alloc(ctx, n1 * F);
-  J.m_us.alloc(ctx, 2 * n1 * per_dir_fields(J.p) * F);
+  J.m_us.alloc(ctx, 2 * n1 * held_fields(J.p) * F);
   J.m_deep.alloc(ctx, std::max<size_t>(slot, 1) * F);
   J.m_gpair.alloc(ctx, P * F);
   J.m_pp.alloc(ctx, 4 * n1 * F);
@@ -742,32 +758,44 @@ void add_smooth_flow(Builder& b, const std::vector<Job*>& jobs) {
 }
 
 
-// Planes per march tile of a launch over these items: the longest chunk that
-// still fills the chip.
+// Planes per march tile of a launch over these items: a block walks zc + 2
+// planes and `slots` blocks walk at once, so longer chunks share the two extra
+// planes and shorter ones leave less of a tail: 0.3 of a block's walk fits the
+// measured ends (six 64^3 fields' adjoint in chunks of 4 / 8 planes 23.5 / 21.7
+// us, one of 97x113x101 in 4 / 8 22.6 / 24.0, six of 160x192x160 in 16 / 32
+// 290 / 284).
 template <class Item>
-void set_march_tiles(std::vector<Item>& items, int& tiles) {
-  int zc = 64;
-  do {
-    zc /= 2;
-    tiles = 0;
-    for (Item& it : items) {
-      it.zc = zc;
-      it.tile0 = tiles;
-      tiles += march_tiles(it.D, it.H, it.W, zc);
+void set_march_tiles(std::vector<Item>& items, int slots, int& tiles) {
+  int best = 2;
+  double best_cost = 1e300;
+  for (int zc = 32; zc >= 2; zc /= 2) {
+    double blocks = 0;
+    for (const Item& it : items) blocks += march_tiles(it.D, it.H, it.W, zc);
+    const double cost = (blocks / slots + 0.3) * (zc + 2);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = zc;
     }
-  } while (zc > 2 && tiles < MARCH_BLOCKS);
+  }
+  tiles = 0;
+  for (Item& it : items) {
+    it.zc = best;
+    it.tile0 = tiles;
+    tiles += march_tiles(it.D, it.H, it.W, best);
+  }
 }
 
 void add_exp_fwd_step(Builder& b, const std::vector<Job*>& jobs, int s, bool recompute_only,
                       int upto) {
   // One squaring s -> s+1 for every direction of every job.  With
-  // recompute_only, this is step s of recomputing u_upto in the scratch slots.
+  // recompute_only, this is step s of forming the ring up to u_upto anew.
   std::vector<ExpFwdItem> items;
   int tiles = 0;
   double bytes = 0;
   for (Job* J : jobs) {
     if (s >= J->K()) continue;
-    if (recompute_only && (J->p.exp_mode != MUSTER_EXP_RECOMPUTE || upto > J->K() - 1)) continue;
+    if (recompute_only && (J->p.exp_mode != MUSTER_EXP_RECOMPUTE || !ring_refill(J->K(), upto)))
+      continue;
     const int* d = J->ldims[J->level];
     const float scale = std::ldexp(1.f, -J->K());
     for (int dir = 0; dir < 2 * (J->N - 1); ++dir) {
@@ -788,7 +816,7 @@ void add_exp_fwd_step(Builder& b, const std::vector<Job*>& jobs, int s, bool rec
       bytes += B_EXP_FWD * J->Vc();
     }
   }
-  set_march_tiles(items, tiles);
+  set_march_tiles(items, EXP_FWD_SLOTS, tiles);
   b.add(ST_EXP_FWD, items, tiles, bytes);
 }
 
@@ -1243,7 +1271,7 @@ void add_backward(Builder& b, const std::vector<Job*>& jobs) {
       f.det_blocks = it.det_blocks;
       folds.push_back(f);
     }
-    set_march_tiles(items, tiles);
+    set_march_tiles(items, EXP_BWD_SLOTS, tiles);
     b.add(ST_EXP_BWD, items, tiles, bytes);
     // the far voxels' pass goes over point tiles
     tiles = 0;
@@ -2178,7 +2206,7 @@ muster_status muster_exp(muster_ctx* h, void* stream, const int dims[3], int K, 
       it.src = s == 0 ? svf : buf(s);
       it.a = s == 0 ? (float)sign * std::ldexp(1.f, -K) : 1.f;
       it.dst = s == K - 1 ? disp : buf(s + 1);
-      set_march_tiles(one, tiles);
+      set_march_tiles(one, EXP_FWD_SLOTS, tiles);
       offs.push_back(sc.add(it));
     }
     sc.upload();
@@ -2205,20 +2233,19 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     StepCall sc{ctx, (hipStream_t)stream, {}};
     const size_t V = (size_t)dims[0] * dims[1] * dims[2];
     const size_t F = 3 * V;
-    const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 0) : 2;
+    const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 1) : ring_slots(K);
     const int ntp = point_tiles(dims[0], dims[1], dims[2]);
     // the last step writes grad_svf unless it still reads what lies there
     const bool direct =
         !overlap(grad_svf, svf, F) && !(K == 1 && overlap(grad_svf, grad_disp, F));
     DevMem us, pp, far;
-    us.alloc(ctx, std::max<size_t>(nstore, 1) * F * sizeof(float));
+    us.alloc(ctx, nstore * F * sizeof(float));
     pp.alloc(ctx, 2 * F * sizeof(float));
     far.alloc(ctx, (size_t)ntp * sizeof(int));
     // zero bits: the marks start clear
     MUSTER_HIP(launch_fill(far.as<float>(), (int64_t)ntp, 0.f, sc.s));
     const float a0 = (float)sign * std::ldexp(1.f, -K);
-    auto ustore = [&](int k) { return us.as<float>() + (size_t)(k - 1) * F; };        // store: u_k
-    auto uscr = [&](int k) { return us.as<float>() + (size_t)((k - 1) % 2) * F; };    // recompute
+    auto ustep = [&](int k) { return us.as<float>() + (size_t)((k - 1) % nstore) * F; };  // u_k
     struct L { int kind; size_t off; int tiles; };
     std::vector<L> seq;
     auto fwd_step = [&](int k, float* src, float* dst) {
@@ -2230,21 +2257,16 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
       it.a = k == 0 ? a0 : 1.f;
       it.dst = dst;
       int mt = 0;
-      set_march_tiles(one, mt);
+      set_march_tiles(one, EXP_FWD_SLOTS, mt);
       seq.push_back({0, sc.add(it), mt});
     };
-    if (mode == MUSTER_EXP_STORE)
-      for (int k = 0; k < K - 1; ++k) fwd_step(k, k == 0 ? nullptr : ustore(k), ustore(k + 1));
+    auto advance = [&](int to) {  // u_1..u_to
+      for (int k = 0; k < to; ++k) fwd_step(k, k == 0 ? nullptr : ustep(k), ustep(k + 1));
+    };
+    advance(K - 1);
     for (int s = K - 1; s >= 0; --s) {
-      const float* us_src;
-      if (s == 0) {
-        us_src = svf;
-      } else if (mode == MUSTER_EXP_STORE) {
-        us_src = ustore(s);
-      } else {
-        for (int k = 0; k < s; ++k) fwd_step(k, k == 0 ? nullptr : uscr(k), uscr(k + 1));
-        us_src = uscr(s);
-      }
+      if (mode == MUSTER_EXP_RECOMPUTE && ring_refill(K, s)) advance(s);
+      const float* us_src = s == 0 ? svf : ustep(s);
       std::vector<ExpBwdItem> one(1);
       ExpBwdItem& it = one[0];
       it = ExpBwdItem{};
@@ -2255,7 +2277,7 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
       it.gout = s == 0 && direct ? grad_svf : pp.as<float>() + (size_t)(s % 2) * F;
       it.far = far.as<int>();
       int mt = 0;
-      set_march_tiles(one, mt);
+      set_march_tiles(one, EXP_BWD_SLOTS, mt);
       seq.push_back({1, sc.add(it), mt});
     }
     sc.upload();

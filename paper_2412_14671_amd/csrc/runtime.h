@@ -127,6 +127,11 @@ struct DevMem {
   T* as() const { return static_cast<T*>(p); }
 };
 
+// Recompute mode: squaring steps kept per direction besides u_K.  Four let the
+// usual K 7 form two steps again (21 with the two a ping-pong needs), in less
+// memory than the adjoint's former staging slots took.
+constexpr int REC_SLOTS = 4;
+
 // One registration job: buffers sized for its finest grid and reused, with
 // the level's own stride, at coarser levels.
 struct Job {
