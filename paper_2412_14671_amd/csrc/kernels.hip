@@ -61,6 +61,22 @@ __device__ __forceinline__ int find_item(const Item* __restrict__ items, int n, 
   return lo;
 }
 
+// Where a kernel finds its item: a table in device memory, or, for calls of one
+// item, the launch's own arguments, which spares the upload and, in every
+// block, a dependent load.
+template <class Item>
+struct Table {
+  const Item* __restrict__ items;
+  int n;
+  __device__ __forceinline__ const Item& at(int tile) const { return items[find_item(items, n, tile)]; }
+};
+
+template <class Item>
+struct One {
+  Item it;
+  __device__ __forceinline__ const Item& at(int) const { return it; }
+};
+
 struct Ax {
   int i0;
   float t;
@@ -497,10 +513,10 @@ __device__ __forceinline__ void sample_cells_lds(const cgfloat* __restrict__ f, 
 // ---------------------------------------------------------------------------
 // Composition forward: out = prev + C o (Omega + prev)   (Eq. cum_deformation)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) GATHER_WAVES void k_compose_fwd(const ComposeItem* __restrict__ items,
-                                                       int n_items, int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(BLOCK) GATHER_WAVES void k_compose_fwd(const Items items, int n_tiles) {
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const ComposeItem it = items[find_item(items, n_items, tile)];
+  const ComposeItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, V = D * H * W;
   const PTile tc = point_tile(tile - it.tile0, H, W);
   const cgfloat* __restrict__ pr = gp(it.prev);
@@ -818,12 +834,12 @@ __device__ __forceinline__ bool is_near(const float (&e)[3]) {
 // (187 vector instructions per voxel, about 100 here): one 160x192x160 field
 // 34.0 -> 28.3 us, six of them at once 38.7 -> 29.8 us per field.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(MT_NT) void k_exp_fwd(const ExpFwdItem* __restrict__ items,
-                                                   int n_items, int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(MT_NT) void k_exp_fwd(const Items items, int n_tiles) {
   constexpr int PX = MT_PX, ROW = 3 * PX, PLANE = MT_PY * ROW;
   __shared__ float up[4 * PLANE];  // a * src of the last planes, [plane & 3][row][component][column]
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const ExpFwdItem it = items[find_item(items, n_items, tile)];
+  const ExpFwdItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const MTile tc = march_tile(tile - it.tile0, D, H, W, it.zc);
   const float a = it.a;
@@ -934,14 +950,14 @@ __global__ __launch_bounds__(MT_NT) void k_exp_fwd(const ExpFwdItem* __restrict_
 // conflicts between a wave's rows; six 160x192x160 fields at once take 284 us,
 // with 16 x 16 columns 361, with 16 x 32 300, with 8 x 16 403, with 4 x 64 324.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(MT_NT) void k_exp_bwd(const ExpBwdItem* __restrict__ items,
-                                                   int n_items, int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tiles) {
   constexpr int PX = MT_PX, ROW = 3 * PX, PLANE = MT_PY * ROW;
   __shared__ float4 ra[2][MT_P1];  // e_z, e_y, e_x, G_z of a plane
   __shared__ float2 rb[2][MT_P1];  // G_y, G_x
   __shared__ float up[4 * PLANE];  // u of the last planes, [plane & 3][row][component][column]
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const ExpBwdItem it = items[find_item(items, n_items, tile)];
+  const ExpBwdItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const MTile tc = march_tile(tile - it.tile0, D, H, W, it.zc);
   const float a = it.a;
@@ -1107,16 +1123,15 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const ExpBwdItem* __restrict_
 // the usual case: displacements reach a voxel only in the last squarings of a
 // large deformation.  The marks are cleared once read.  DETMAX: the
 // deterministic mode's reduce-only pass (no writes but the job's slot).
-template <bool DETMAX>
-__global__ __launch_bounds__(BLOCK) void k_exp_far(const ExpBwdItem* __restrict__ items, int n_items,
-                                                   int n_tiles, int group) {
+template <bool DETMAX, class Items>
+__global__ __launch_bounds__(BLOCK) void k_exp_far(const Items items, int n_tiles, int group) {
   __shared__ __align__(16) int acc[DETMAX ? 4 : 3 * SCATTER_CELLS];
   __shared__ int sred[8 * (BLOCK / 64)];
   const int lane = threadIdx.x & 63;
   const int mine = blockIdx.x * group + lane;
   int mark = 0;
   if (lane < group && mine < n_tiles) {
-    const ExpBwdItem& m = items[find_item(items, n_items, mine)];
+    const ExpBwdItem& m = items.at(mine);
     mark = m.far[mine - m.tile0];
   }
   uint64_t todo = __ballot(mark != 0);  // the same in every wave of the block
@@ -1125,7 +1140,7 @@ __global__ __launch_bounds__(BLOCK) void k_exp_far(const ExpBwdItem* __restrict_
   while (todo) {
     const int tile = blockIdx.x * group + __builtin_ctzll(todo);
     todo &= todo - 1;
-    const ExpBwdItem it = items[find_item(items, n_items, tile)];
+    const ExpBwdItem it = items.at(tile);
     const int D = it.D, H = it.H, W = it.W, V = D * H * W;
     const PTile tc = point_tile(tile - it.tile0, H, W);
     const cgfloat* __restrict__ s = gp(it.src);
@@ -1174,11 +1189,11 @@ __global__ __launch_bounds__(BLOCK) void k_exp_far(const ExpBwdItem* __restrict_
 // in registers and those in the plane come from cache, so the field is read
 // from memory once and the kernel moves 12 bytes per field named in the item.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const CombineItem* __restrict__ items,
-                                                         int n_items, int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int n_tiles) {
   __shared__ double red[CT_Y * CT_X / 64];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const CombineItem it = items[find_item(items, n_items, tile)];
+  const CombineItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const int local = tile - it.tile0;
   const int ntx = (W + CT_X - 1) / CT_X, nty = (H + CT_Y - 1) / CT_Y;
@@ -1286,13 +1301,12 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const CombineItem* __re
 constexpr int CB_NT = 2 * BLOCK, CB_VP = PT_VOX / CB_NT;
 static_assert(BLOCK % 64 == 0 && CB_NT % 64 == 0, "blocks of whole waves (ld_to_lds)");
 
-template <bool DETMAX>
-__global__ __launch_bounds__(CB_NT) void k_compose_bwd(const ComposeBwdItem* __restrict__ items,
-                                                       int n_items, int n_tiles) {
+template <bool DETMAX, class Items>
+__global__ __launch_bounds__(CB_NT) void k_compose_bwd(const Items items, int n_tiles) {
   __shared__ __align__(16) int acc[3 * SCATTER_CELLS];
   __shared__ int sred[16 * (CB_NT / 64)];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const ComposeBwdItem it = items[find_item(items, n_items, tile)];
+  const ComposeBwdItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const PTile tc = point_tile(tile - it.tile0, H, W);
   const cgfloat* __restrict__ C = gp(it.C);
@@ -1533,10 +1547,10 @@ __device__ __forceinline__ float window_sum(float (&ring)[WN], float& pre, int j
 
 // Warp of the source image by the pair field (Sec. 2.1): M(p) = I(p + U(p)),
 // with the rigid adjustment of the source session added to U (Sec. 2.5).
-__global__ __launch_bounds__(BLOCK) void k_warp(const SimItem* __restrict__ items, int n_items,
-                                                int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(BLOCK) void k_warp(const Items items, int n_tiles) {
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const SimItem it = items[find_item(items, n_items, tile)];
+  const SimItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const PTile tc = point_tile(tile - it.tile0, H, W);
   const cgfloat* __restrict__ I = gp(it.I);
@@ -1609,16 +1623,15 @@ struct Box {
   static_assert(TX % SEG == 0 && TY % SEG == 0 && YT <= NT, "tile not a multiple of the segments");
 };
 
-template <int R, int TY, int TX>
-__global__ __launch_bounds__(TY * TX) void k_sim_stats(const SimItem* __restrict__ items, int n_items,
-                                                       int n_tiles, int metric) {
+template <int R, int TY, int TX, class Items>
+__global__ __launch_bounds__(TY * TX) void k_sim_stats(const Items items, int n_tiles, int metric) {
   using B = Box<R, TY, TX>;
   constexpr int WN = B::WN, PX = B::PX, P1 = B::P1, NS = B::NS, NT = B::NT;
   __shared__ float zs[5 * (B::ZQ > B::YQ ? B::ZQ : B::YQ)];  // z-sums; then the finished sums
   __shared__ float xs[5 * B::XQ];
   __shared__ double red[NT / 64];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const SimItem it = items[find_item(items, n_items, tile)];
+  const SimItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   // the block's columns, its chunk [c0, c1) and its part [z0, z1) of it
   const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, 1);
@@ -1829,16 +1842,15 @@ __global__ __launch_bounds__(TY * TX) void k_sim_stats(const SimItem* __restrict
 // The window sums of the coefficients are formed like those of k_sim_stats.
 // The field at an output voxel is loaded two slices ahead of its use, the
 // corners of the cell it samples one slice ahead.
-template <int R, int TY, int TX>
-__global__ __launch_bounds__(TY * TX) void k_sim_grad(const SimItem* __restrict__ items, int n_items,
-                                                      int n_tiles) {
+template <int R, int TY, int TX, class Items>
+__global__ __launch_bounds__(TY * TX) void k_sim_grad(const Items items, int n_tiles) {
   using B = Win<R, TY, TX>;
   constexpr int NT = B::NT, NS = B::NS, WN = B::WN, XT = B::XT, XQ = B::XQ;
   static_assert(3 * XT <= NT, "one x-sum task per thread");
   __shared__ float raw[2][3][B::SLICE];
   __shared__ float xs[2][3 * XQ];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const SimItem it = items[find_item(items, n_items, tile)];
+  const SimItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, it.zg);
   const cgfloat* __restrict__ F = gp(it.F);
@@ -2183,10 +2195,10 @@ __global__ void k_finish(JobState* const* __restrict__ states, int n_jobs) {
 // ---------------------------------------------------------------------------
 // Pyramid (Sec. 2.7)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_pool2(const PoolItem* __restrict__ items, int n_items,
-                                                 int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(BLOCK) void k_pool2(const Items items, int n_tiles) {
   const int tile = blockIdx.x;
-  const PoolItem it = items[find_item(items, n_items, tile)];
+  const PoolItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W;
   const int D2 = D / 2, H2 = H / 2, W2 = W / 2;
   const int n = D2 * H2 * W2;
@@ -2206,14 +2218,14 @@ __global__ __launch_bounds__(BLOCK) void k_pool2(const PoolItem* __restrict__ it
 // A block stages the coarse cells behind a tile of UF_TZ x UF_TY x UF_TX fine
 // voxels (t/2 + 2 per axis, three components, coordinates clamped to the
 // grid) in LDS; every fine voxel then reads its 8 corners from there.
-__global__ __launch_bounds__(BLOCK) void k_upsample2(const UpItem* __restrict__ items, int n_items,
-                                                     int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(BLOCK) void k_upsample2(const Items items, int n_tiles) {
   constexpr int CZ = UF_TZ / 2 + 2, CY = UF_TY / 2 + 2, CX = UF_TX / 2 + 2, CN = CZ * CY * CX;
   constexpr int PER = UF_TZ * UF_TY * UF_TX / BLOCK;
   static_assert(UF_TY * UF_TX == BLOCK, "one fine slice of the tile per thread pass");
   __shared__ float cs[3 * CN];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const UpItem it = items[find_item(items, n_items, tile)];
+  const UpItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
   const int D2 = 2 * D, H2 = 2 * H, W2 = 2 * W;
   const int n = D2 * H2 * W2;
@@ -2268,8 +2280,8 @@ __device__ __forceinline__ float up_weight(int f, int c, int n) {
 // LDS, one component at a time, and sums along x, then y, then z, with the
 // 4 weights per coarse index of each axis computed once per block: every fine
 // sample is read from HBM once and the 64-tap gather becomes 3 x 4 taps.
-__global__ __launch_bounds__(BLOCK) void k_upsample2_adj(const UpItem* __restrict__ items,
-                                                         int n_items, int n_tiles) {
+template <class Items>
+__global__ __launch_bounds__(BLOCK) void k_upsample2_adj(const Items items, int n_tiles) {
   constexpr int FZ = 2 * UA_TZ + 2, FY = 2 * UA_TY + 2, FX = 2 * UA_TX + 2;
   constexpr int FN = FZ * FY * FX;           // fine region; later the y sums
   constexpr int S1 = FZ * FY * UA_TX;        // x sums
@@ -2280,7 +2292,7 @@ __global__ __launch_bounds__(BLOCK) void k_upsample2_adj(const UpItem* __restric
   __shared__ float s1[S1];
   __shared__ float wz[UA_TZ][4], wy[UA_TY][4], wx[UA_TX][4];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
-  const UpItem it = items[find_item(items, n_items, tile)];
+  const UpItem it = items.at(tile);
   const int D = it.D, H = it.H, W = it.W, V = D * H * W;
   const int D2 = 2 * D, H2 = 2 * H, W2 = 2 * W, n2 = 8 * V;
   const int local = tile - it.tile0;
@@ -2400,36 +2412,50 @@ void set_launch_events(hipEvent_t start, hipEvent_t stop) {
       hipLaunchKernelGGL(kernel, grid, block, shm, stream, __VA_ARGS__);                      \
   } while (0)
 
-hipError_t launch_exp_fwd(const ExpFwdItem* items, int n_items, int n_tiles, hipStream_t s) {
+template <class Items>
+static hipError_t exp_fwd_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_exp_fwd, dim3(n_tiles), dim3(MT_NT), 0, s, items, n_items, n_tiles);
+  MUSTER_LAUNCH(k_exp_fwd<Items>, dim3(n_tiles), dim3(MT_NT), 0, s, items, n_tiles);
   return hipGetLastError();
 }
 
-hipError_t launch_compose_fwd(const ComposeItem* items, int n_items, int n_tiles, hipStream_t s) {
+template <class Items>
+static hipError_t compose_fwd_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_compose_fwd, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_items, n_tiles);
+  MUSTER_LAUNCH(k_compose_fwd<Items>, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_tiles);
   return hipGetLastError();
 }
 
 // Marks per block of k_exp_far: blocks that look at more end sooner where none
 // is set (28800 marks in eights: 6 us), but take their marked tiles one after
 // another.
-static int far_group(int n_tiles) { return n_tiles < 4096 ? 1 : n_tiles < 16384 ? 4 : 8; }
-
-hipError_t launch_exp_far_detmax(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s) {
+template <bool DETMAX, class Items>
+static hipError_t exp_far_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  const int group = far_group(n_tiles);
-  MUSTER_LAUNCH(k_exp_far<true>, dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items, n_items,
+  const int group = n_tiles < 4096 ? 1 : n_tiles < 16384 ? 4 : 8;
+  MUSTER_LAUNCH((k_exp_far<DETMAX, Items>), dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items,
                 n_tiles, group);
   return hipGetLastError();
 }
 
-hipError_t launch_exp_far(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s) {
+template <class Items>
+static hipError_t exp_bwd_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  const int group = far_group(n_tiles);
-  MUSTER_LAUNCH(k_exp_far<false>, dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items, n_items,
-                n_tiles, group);
+  MUSTER_LAUNCH(k_exp_bwd<Items>, dim3(n_tiles), dim3(MT_NT), 0, s, items, n_tiles);
+  return hipGetLastError();
+}
+
+template <class Items>
+static hipError_t combine_(const Items& items, int n_tiles, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  MUSTER_LAUNCH(k_combine<Items>, dim3(n_tiles), dim3(CT_Y * CT_X), 0, s, items, n_tiles);
+  return hipGetLastError();
+}
+
+template <bool DETMAX, class Items>
+static hipError_t compose_bwd_(const Items& items, int n_tiles, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  MUSTER_LAUNCH((k_compose_bwd<DETMAX, Items>), dim3(n_tiles), dim3(CB_NT), 0, s, items, n_tiles);
   return hipGetLastError();
 }
 
@@ -2445,80 +2471,114 @@ hipError_t launch_det_clear(JobState* const* states, int n_jobs, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_exp_bwd(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_exp_bwd, dim3(n_tiles), dim3(MT_NT), 0, s, items, n_items, n_tiles);
+template <int R, int TY, int TX, class Items>
+static void sim_launch(bool grad, const Items& items, int n_tiles, int metric, hipStream_t s) {
+  if (grad)
+    MUSTER_LAUNCH((k_sim_grad<R, TY, TX, Items>), dim3(n_tiles), dim3(TY * TX), 0, s, items, n_tiles);
+  else
+    MUSTER_LAUNCH((k_sim_stats<R, TY, TX, Items>), dim3(n_tiles), dim3(TY * TX), 0, s, items, n_tiles,
+                  metric);
+}
+
+template <int R, class Items>
+static hipError_t sim_shape(bool grad, const Items& items, int n_tiles, int metric, int shape,
+                            hipStream_t s) {
+  switch (shape) {
+    case 0: sim_launch<R, 8, 32>(grad, items, n_tiles, metric, s); break;
+    case 1: sim_launch<R, 16, 32>(grad, items, n_tiles, metric, s); break;
+    case 2: sim_launch<R, 8, 64>(grad, items, n_tiles, metric, s); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_combine(const CombineItem* items, int n_items, int n_tiles, hipStream_t s) {
+template <class Items>
+static hipError_t sim_window(bool grad, const Items& items, int n_tiles, int window, int metric,
+                             int shape, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_combine, dim3(n_tiles), dim3(CT_Y * CT_X), 0, s, items, n_items, n_tiles);
+  switch (window) {
+    case 3: return sim_shape<1>(grad, items, n_tiles, metric, shape, s);
+    case 5: return sim_shape<2>(grad, items, n_tiles, metric, shape, s);
+    case 7: return sim_shape<3>(grad, items, n_tiles, metric, shape, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <class Items>
+static hipError_t warp_(const Items& items, int n_tiles, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  MUSTER_LAUNCH(k_warp<Items>, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_tiles);
   return hipGetLastError();
 }
 
-hipError_t launch_compose_bwd(const ComposeBwdItem* items, int n_items, int n_tiles,
-                              hipStream_t s) {
+template <class Items>
+static hipError_t pool2_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_compose_bwd<false>, dim3(n_tiles), dim3(CB_NT), 0, s, items, n_items, n_tiles);
+  MUSTER_LAUNCH(k_pool2<Items>, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_tiles);
   return hipGetLastError();
+}
+
+template <class Items>
+static hipError_t upsample2_(const Items& items, int n_tiles, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  MUSTER_LAUNCH(k_upsample2<Items>, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_tiles);
+  return hipGetLastError();
+}
+
+template <class Items>
+static hipError_t upsample2_adj_(const Items& items, int n_tiles, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  MUSTER_LAUNCH(k_upsample2_adj<Items>, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_tiles);
+  return hipGetLastError();
+}
+
+// Each launcher for a table of items in device memory, and for one item that
+// travels with the launch.
+#define MUSTER_BOTH(name, Item, call)                                                              \
+  hipError_t launch_##name(const Item* items, int n_items, int n_tiles, hipStream_t s) {           \
+    return call(Table<Item>{items, n_items}, n_tiles, s);                                          \
+  }                                                                                                \
+  hipError_t launch_##name(const Item& one, int n_tiles, hipStream_t s) {                          \
+    return call(One<Item>{one}, n_tiles, s);                                                       \
+  }
+MUSTER_BOTH(exp_fwd, ExpFwdItem, exp_fwd_)
+MUSTER_BOTH(compose_fwd, ComposeItem, compose_fwd_)
+MUSTER_BOTH(exp_bwd, ExpBwdItem, exp_bwd_)
+MUSTER_BOTH(exp_far, ExpBwdItem, exp_far_<false>)
+MUSTER_BOTH(combine, CombineItem, combine_)
+MUSTER_BOTH(compose_bwd, ComposeBwdItem, compose_bwd_<false>)
+MUSTER_BOTH(warp, SimItem, warp_)
+MUSTER_BOTH(pool2, PoolItem, pool2_)
+MUSTER_BOTH(upsample2, UpItem, upsample2_)
+MUSTER_BOTH(upsample2_adj, UpItem, upsample2_adj_)
+#undef MUSTER_BOTH
+
+hipError_t launch_exp_far_detmax(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s) {
+  return exp_far_<true>(Table<ExpBwdItem>{items, n_items}, n_tiles, s);
 }
 
 hipError_t launch_compose_bwd_detmax(const ComposeBwdItem* items, int n_items, int n_tiles,
                                      hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_compose_bwd<true>, dim3(n_tiles), dim3(CB_NT), 0, s, items, n_items, n_tiles);
-  return hipGetLastError();
-}
-
-template <int R, int TY, int TX>
-static void sim_launch(bool grad, const SimItem* items, int n_items, int n_tiles, int metric,
-                       hipStream_t s) {
-  if (grad)
-    MUSTER_LAUNCH((k_sim_grad<R, TY, TX>), dim3(n_tiles), dim3(TY * TX), 0, s, items, n_items,
-                       n_tiles);
-  else
-    MUSTER_LAUNCH((k_sim_stats<R, TY, TX>), dim3(n_tiles), dim3(TY * TX), 0, s, items,
-                       n_items, n_tiles, metric);
-}
-
-template <int R>
-static hipError_t sim_shape(bool grad, const SimItem* items, int n_items, int n_tiles, int metric,
-                            int shape, hipStream_t s) {
-  switch (shape) {
-    case 0: sim_launch<R, 8, 32>(grad, items, n_items, n_tiles, metric, s); break;
-    case 1: sim_launch<R, 16, 32>(grad, items, n_items, n_tiles, metric, s); break;
-    case 2: sim_launch<R, 8, 64>(grad, items, n_items, n_tiles, metric, s); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-static hipError_t sim_window(bool grad, const SimItem* items, int n_items, int n_tiles, int window,
-                             int metric, int shape, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  switch (window) {
-    case 3: return sim_shape<1>(grad, items, n_items, n_tiles, metric, shape, s);
-    case 5: return sim_shape<2>(grad, items, n_items, n_tiles, metric, shape, s);
-    case 7: return sim_shape<3>(grad, items, n_items, n_tiles, metric, shape, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t launch_warp(const SimItem* items, int n_items, int n_tiles, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_warp, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_items, n_tiles);
-  return hipGetLastError();
+  return compose_bwd_<true>(Table<ComposeBwdItem>{items, n_items}, n_tiles, s);
 }
 
 hipError_t launch_sim_stats(const SimItem* items, int n_items, int n_tiles, int window, int metric,
                             int shape, hipStream_t s) {
-  return sim_window(false, items, n_items, n_tiles, window, metric, shape, s);
+  return sim_window(false, Table<SimItem>{items, n_items}, n_tiles, window, metric, shape, s);
+}
+
+hipError_t launch_sim_stats(const SimItem& one, int n_tiles, int window, int metric, int shape,
+                            hipStream_t s) {
+  return sim_window(false, One<SimItem>{one}, n_tiles, window, metric, shape, s);
 }
 
 hipError_t launch_sim_grad(const SimItem* items, int n_items, int n_tiles, int window, int shape,
                            hipStream_t s) {
-  return sim_window(true, items, n_items, n_tiles, window, 0, shape, s);
+  return sim_window(true, Table<SimItem>{items, n_items}, n_tiles, window, 0, shape, s);
+}
+
+hipError_t launch_sim_grad(const SimItem& one, int n_tiles, int window, int shape, hipStream_t s) {
+  return sim_window(true, One<SimItem>{one}, n_tiles, window, 0, shape, s);
 }
 
 hipError_t launch_adam(const AdamItem* items, int n_items, int n_tiles, hipStream_t s) {
@@ -2559,12 +2619,6 @@ hipError_t launch_pattern(float* p, int64_t n, const int dims[3], float off, flo
 hipError_t launch_finish(JobState* const* states, int n_jobs, hipStream_t s) {
   if (n_jobs <= 0) return hipSuccess;
   MUSTER_LAUNCH(k_finish, dim3(ceil_div(n_jobs, 64)), dim3(64), 0, s, states, n_jobs);
-  return hipGetLastError();
-}
-
-hipError_t launch_pool2(const PoolItem* items, int n_items, int n_tiles, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_pool2, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_items, n_tiles);
   return hipGetLastError();
 }
 
@@ -2788,18 +2842,6 @@ hipError_t launch_add_rigid(GridDims d, float* field, const RigidState* rg, hipS
   if (V <= 0) return hipSuccess;
   const int blocks = ceil_div(V, BLOCK) < 2048 ? ceil_div(V, BLOCK) : 2048;
   MUSTER_LAUNCH(k_add_rigid, dim3(blocks), dim3(BLOCK), 0, s, d, field, rg);
-  return hipGetLastError();
-}
-
-hipError_t launch_upsample2_adj(const UpItem* items, int n_items, int n_tiles, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_upsample2_adj, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_items, n_tiles);
-  return hipGetLastError();
-}
-
-hipError_t launch_upsample2(const UpItem* items, int n_items, int n_tiles, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  MUSTER_LAUNCH(k_upsample2, dim3(n_tiles), dim3(BLOCK), 0, s, items, n_items, n_tiles);
   return hipGetLastError();
 }
 

@@ -356,17 +356,25 @@ inline int grad_tiles(int D, int H, int W, int zg, int shape) {
   return ceil_div(D, zg) * sim_cols(H, W, shape);
 }
 
-// Launchers (kernels.hip).  All return hipError_t of the launch.
+// Launchers (kernels.hip).  All return hipError_t of the launch.  Those of a
+// table of items in device memory have a twin for one item, which travels with
+// the launch's arguments.
 // Start and stop events for every following launch on this thread (null:
 // untimed).  Each plan stage is one launch.
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
 hipError_t launch_exp_fwd(const ExpFwdItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_exp_fwd(const ExpFwdItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_compose_fwd(const ComposeItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_compose_fwd(const ComposeItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_exp_bwd(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_exp_bwd(const ExpBwdItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_exp_far(const ExpBwdItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_exp_far(const ExpBwdItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_combine(const CombineItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_combine(const CombineItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_compose_bwd(const ComposeBwdItem* items, int n_items, int n_tiles,
                               hipStream_t s);
+hipError_t launch_compose_bwd(const ComposeBwdItem& one, int n_tiles, hipStream_t s);
 // Deterministic mode: the passes of the composition and Exp adjoints that
 // only reduce each job's largest block magnitude into its slot (no other
 // writes), the fold of the fixed-point fields, and the clearing of the slots.
@@ -377,10 +385,14 @@ hipError_t launch_det_fold(const DetFoldItem* items, int n_items, int n_tiles, h
 hipError_t launch_det_clear(JobState* const* states, int n_jobs, hipStream_t s);
 // M = I o (Omega + U) of each item, over point tiles of its grid.
 hipError_t launch_warp(const SimItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_warp(const SimItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_sim_stats(const SimItem* items, int n_items, int n_tiles, int window, int metric,
                             int shape, hipStream_t s);
+hipError_t launch_sim_stats(const SimItem& one, int n_tiles, int window, int metric, int shape,
+                            hipStream_t s);
 hipError_t launch_sim_grad(const SimItem* items, int n_items, int n_tiles, int window, int shape,
                            hipStream_t s);
+hipError_t launch_sim_grad(const SimItem& one, int n_tiles, int window, int shape, hipStream_t s);
 hipError_t launch_adam(const AdamItem* items, int n_items, int n_tiles, hipStream_t s);
 hipError_t launch_smooth(const SmoothItem* items, int n_items, int n_tiles, int lds_floats,
                          hipStream_t s);
@@ -391,9 +403,12 @@ int smooth_item_setup(SmoothItem& it, const int dims[3], int axis, float sigma, 
 int smooth_radius(int n, float sigma);
 hipError_t launch_finish(JobState* const* states, int n_jobs, hipStream_t s);
 hipError_t launch_pool2(const PoolItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_pool2(const PoolItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_upsample2(const UpItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_upsample2(const UpItem& one, int n_tiles, hipStream_t s);
 // adjoint: src [3][2D][2H][2W] (fine), dst [3][D][H][W] (coarse), tiles over the coarse grid
 hipError_t launch_upsample2_adj(const UpItem* items, int n_items, int n_tiles, hipStream_t s);
+hipError_t launch_upsample2_adj(const UpItem& one, int n_tiles, hipStream_t s);
 hipError_t launch_adam_flat(int64_t n, float* x, const float* g, float* m, float* v, int t,
                             float lr, float b1, float b2, float eps, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t n, float v, hipStream_t s);

@@ -385,9 +385,9 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
 
 // Small item tables used outside plans (pyramid, upsampling) go through this
 // helper: upload, launch, synchronise.
-template <class Item, class Launch>
+template <class Item>
 static void run_items(Ctx* ctx, std::vector<Item>& items, int n_tiles, hipStream_t s,
-                      Launch&& launch) {
+                      hipError_t (*launch)(const Item*, int, int, hipStream_t)) {
   if (items.empty() || n_tiles <= 0) return;
   DevMem d;
   d.alloc(ctx, items.size() * sizeof(Item));
@@ -2188,7 +2188,7 @@ muster_status muster_exp(muster_ctx* h, void* stream, const int dims[3], int K, 
     NEED(K >= 1 && K <= 20, "K must be in 1..20");
     NEED(sign == 1 || sign == -1, "sign must be +1 or -1");
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     const size_t V = (size_t)dims[0] * dims[1] * dims[2];
     DevMem tmp;
     if (!steps) tmp.alloc(ctx, 2 * 3 * V * sizeof(float));
@@ -2197,7 +2197,6 @@ muster_status muster_exp(muster_ctx* h, void* stream, const int dims[3], int K, 
       return tmp.as<float>() + (size_t)((k - 1) % 2) * 3 * V;
     };
     int tiles = 0;
-    std::vector<size_t> offs;
     for (int s = 0; s < K; ++s) {
       std::vector<ExpFwdItem> one(1);
       ExpFwdItem& it = one[0];
@@ -2207,15 +2206,12 @@ muster_status muster_exp(muster_ctx* h, void* stream, const int dims[3], int K, 
       it.a = s == 0 ? (float)sign * std::ldexp(1.f, -K) : 1.f;
       it.dst = s == K - 1 ? disp : buf(s + 1);
       set_march_tiles(one, EXP_FWD_SLOTS, tiles);
-      offs.push_back(sc.add(it));
+      MUSTER_HIP(launch_exp_fwd(it, tiles, hs));
     }
-    sc.upload();
-    for (int s = 0; s < K; ++s)
-      MUSTER_HIP(launch_exp_fwd((const ExpFwdItem*)(sc.dev() + offs[s]), 1, tiles, sc.s));
     if (steps)
       MUSTER_HIP(hipMemcpyAsync(steps + (size_t)(K - 1) * 3 * V, disp, 3 * V * sizeof(float),
-                                hipMemcpyDeviceToDevice, sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+                                hipMemcpyDeviceToDevice, hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2230,7 +2226,7 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     mode &= ~MUSTER_EXP_FLAT;
     NEED(mode == MUSTER_EXP_STORE || mode == MUSTER_EXP_RECOMPUTE, "bad mode");
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     const size_t V = (size_t)dims[0] * dims[1] * dims[2];
     const size_t F = 3 * V;
     const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 1) : ring_slots(K);
@@ -2243,11 +2239,9 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     pp.alloc(ctx, 2 * F * sizeof(float));
     far.alloc(ctx, (size_t)ntp * sizeof(int));
     // zero bits: the marks start clear
-    MUSTER_HIP(launch_fill(far.as<float>(), (int64_t)ntp, 0.f, sc.s));
+    MUSTER_HIP(launch_fill(far.as<float>(), (int64_t)ntp, 0.f, hs));
     const float a0 = (float)sign * std::ldexp(1.f, -K);
     auto ustep = [&](int k) { return us.as<float>() + (size_t)((k - 1) % nstore) * F; };  // u_k
-    struct L { int kind; size_t off; int tiles; };
-    std::vector<L> seq;
     auto fwd_step = [&](int k, float* src, float* dst) {
       std::vector<ExpFwdItem> one(1);
       ExpFwdItem& it = one[0];
@@ -2258,7 +2252,7 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
       it.dst = dst;
       int mt = 0;
       set_march_tiles(one, EXP_FWD_SLOTS, mt);
-      seq.push_back({0, sc.add(it), mt});
+      MUSTER_HIP(launch_exp_fwd(it, mt, hs));
     };
     auto advance = [&](int to) {  // u_1..u_to
       for (int k = 0; k < to; ++k) fwd_step(k, k == 0 ? nullptr : ustep(k), ustep(k + 1));
@@ -2278,21 +2272,13 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
       it.far = far.as<int>();
       int mt = 0;
       set_march_tiles(one, EXP_BWD_SLOTS, mt);
-      seq.push_back({1, sc.add(it), mt});
-    }
-    sc.upload();
-    for (auto& l : seq) {
-      const unsigned char* p = sc.dev() + l.off;
-      if (l.kind == 0) {
-        MUSTER_HIP(launch_exp_fwd((const ExpFwdItem*)p, 1, l.tiles, sc.s));
-      } else {
-        MUSTER_HIP(launch_exp_bwd((const ExpBwdItem*)p, 1, l.tiles, sc.s));
-        MUSTER_HIP(launch_exp_far((const ExpBwdItem*)p, 1, ntp, sc.s));
-      }
+      MUSTER_HIP(launch_exp_bwd(it, mt, hs));
+      it.tile0 = 0;
+      MUSTER_HIP(launch_exp_far(it, ntp, hs));
     }
     if (!direct)
-      MUSTER_HIP(hipMemcpyAsync(grad_svf, pp.p, F * sizeof(float), hipMemcpyDeviceToDevice, sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+      MUSTER_HIP(hipMemcpyAsync(grad_svf, pp.p, F * sizeof(float), hipMemcpyDeviceToDevice, hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2303,17 +2289,14 @@ muster_status muster_compose(muster_ctx* h, void* stream, const int dims[3], con
     NEED(ctx && U_prev && Cf && out, "NULL argument");
     check_dims(dims, 2);
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     ComposeItem it{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.prev = U_prev;
     it.C = Cf;
     it.out = out;
-    const size_t off = sc.add(it);
-    sc.upload();
-    MUSTER_HIP(launch_compose_fwd((const ComposeItem*)(sc.dev() + off), 1,
-                                  point_tiles(dims[0], dims[1], dims[2]), sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+    MUSTER_HIP(launch_compose_fwd(it, point_tiles(dims[0], dims[1], dims[2]), hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2324,7 +2307,7 @@ muster_status muster_compose_bwd(muster_ctx* h, void* stream, const int dims[3],
     NEED(ctx && U_prev && Cf && G && G_prev && G_C, "NULL argument");
     check_dims(dims, 2);
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     ComposeBwdItem it{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.g = G;
@@ -2333,11 +2316,8 @@ muster_status muster_compose_bwd(muster_ctx* h, void* stream, const int dims[3],
     it.gprev = G_prev;
     it.gc = G_C;
     it.prev_atomic = 1;
-    const size_t off = sc.add(it);
-    sc.upload();
-    MUSTER_HIP(launch_compose_bwd((const ComposeBwdItem*)(sc.dev() + off), 1,
-                                  point_tiles(dims[0], dims[1], dims[2]), sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+    MUSTER_HIP(launch_compose_bwd(it, point_tiles(dims[0], dims[1], dims[2]), hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2351,13 +2331,13 @@ muster_status muster_sim(muster_ctx* h, void* stream, const int dims[3], int win
     NEED(metric == MUSTER_METRIC_LNCC || metric == MUSTER_METRIC_SILNCC, "unknown metric");
     check_dims(dims, window);
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     const size_t V = (size_t)dims[0] * dims[1] * dims[2];
     DevMem coef, warped;
     if (grad_U) coef.alloc(ctx, 3 * V * sizeof(float));
     warped.alloc(ctx, V * sizeof(float));
     const int r = (window - 1) / 2;
-    const SimTile tl = choose_sim_tile(ctx, dims, window, metric, sc.s);
+    const SimTile tl = choose_sim_tile(ctx, dims, window, metric, hs);
     std::vector<SimItem> one(1);
     SimItem& it = one[0];
     it = SimItem{};
@@ -2373,20 +2353,15 @@ muster_status muster_sim(muster_ctx* h, void* stream, const int dims[3], int win
     it.inv_nr = 1.0 / ((double)(dims[0] - 2 * r) * (dims[1] - 2 * r) * (dims[2] - 2 * r));
     it.js = nullptr;
     it.sim_out = ctx->step_acc;
-    const size_t off = sc.add(it);
-    sc.upload();
-    MUSTER_HIP(hipMemsetAsync(ctx->step_acc, 0, sizeof(double), sc.s));
-    MUSTER_HIP(launch_warp((const SimItem*)(sc.dev() + off), 1,
-                           point_tiles(dims[0], dims[1], dims[2]), sc.s));
+    MUSTER_HIP(launch_fill(reinterpret_cast<float*>(ctx->step_acc), 2, 0.f, hs));
+    MUSTER_HIP(launch_warp(it, point_tiles(dims[0], dims[1], dims[2]), hs));
     const int tiles = stat_tiles(it.D, it.H, it.W, it.zc, it.zs, tl.shape),
               gtiles = grad_tiles(it.D, it.H, it.W, it.zg, tl.shape);
-    MUSTER_HIP(launch_sim_stats((const SimItem*)(sc.dev() + off), 1, tiles, window, metric,
-                                tl.shape, sc.s));
+    MUSTER_HIP(launch_sim_stats(it, tiles, window, metric, tl.shape, hs));
     if (grad_U)
-      MUSTER_HIP(launch_sim_grad((const SimItem*)(sc.dev() + off), 1, gtiles, window, tl.shape,
-                                 sc.s));
-    MUSTER_HIP(hipMemcpyAsync(sim_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+      MUSTER_HIP(launch_sim_grad(it, gtiles, window, tl.shape, hs));
+    MUSTER_HIP(hipMemcpyAsync(sim_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2409,7 +2384,7 @@ muster_status muster_sim_noalloc(muster_ctx* h, void* stream, const int dims[3],
          (size_t)NOALLOC_MAX_VOXELS);
     NEED(ctx->noalloc_scratch, "no scratch on this device");
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     unsigned char* base = static_cast<unsigned char*>(ctx->noalloc_scratch);
     double* sum = reinterpret_cast<double*>(base);
     // the tiling the context already holds for this shape, never a new
@@ -2441,21 +2416,16 @@ muster_status muster_sim_noalloc(muster_ctx* h, void* stream, const int dims[3],
     it.inv_nr = 1.0 / ((double)(dims[0] - 2 * r) * (dims[1] - 2 * r) * (dims[2] - 2 * r));
     it.js = nullptr;
     it.sim_out = sum;
-    const size_t off = sc.add(it);
-    sc.upload();
     // the sum starts at zero: a fill kernel (two floats of zero bits)
-    MUSTER_HIP(launch_fill(reinterpret_cast<float*>(sum), 2, 0.f, sc.s));
-    MUSTER_HIP(launch_warp((const SimItem*)(sc.dev() + off), 1,
-                           point_tiles(dims[0], dims[1], dims[2]), sc.s));
+    MUSTER_HIP(launch_fill(reinterpret_cast<float*>(sum), 2, 0.f, hs));
+    MUSTER_HIP(launch_warp(it, point_tiles(dims[0], dims[1], dims[2]), hs));
     const int tiles = stat_tiles(it.D, it.H, it.W, it.zc, it.zs, tl.shape),
               gtiles = grad_tiles(it.D, it.H, it.W, it.zg, tl.shape);
-    MUSTER_HIP(launch_sim_stats((const SimItem*)(sc.dev() + off), 1, tiles, window, metric,
-                                tl.shape, sc.s));
+    MUSTER_HIP(launch_sim_stats(it, tiles, window, metric, tl.shape, hs));
     if (grad_U)
-      MUSTER_HIP(launch_sim_grad((const SimItem*)(sc.dev() + off), 1, gtiles, window, tl.shape,
-                                 sc.s));
-    MUSTER_HIP(hipMemcpyAsync(sim_host, sum, sizeof(double), hipMemcpyDeviceToHost, sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+      MUSTER_HIP(launch_sim_grad(it, gtiles, window, tl.shape, hs));
+    MUSTER_HIP(hipMemcpyAsync(sim_host, sum, sizeof(double), hipMemcpyDeviceToHost, hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2480,7 +2450,7 @@ muster_status muster_reg(muster_ctx* h, void* stream, const int dims[3], const f
     NEED(ctx && phi && reg_host, "NULL argument");
     check_dims(dims, 2);
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     CombineItem it{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.flow = phi;
@@ -2488,13 +2458,10 @@ muster_status muster_reg(muster_ctx* h, void* stream, const int dims[3], const f
     it.gmul = it.reg_w = 1.f;
     it.loss = ctx->step_acc;
     it.reg_loss_w = 1.0;
-    const size_t off = sc.add(it);
-    sc.upload();
-    MUSTER_HIP(hipMemsetAsync(ctx->step_acc, 0, sizeof(double), sc.s));
-    MUSTER_HIP(launch_combine((const CombineItem*)(sc.dev() + off), 1,
-                              combine_tiles(dims[0], dims[1], dims[2]), sc.s));
-    MUSTER_HIP(hipMemcpyAsync(reg_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+    MUSTER_HIP(launch_fill(reinterpret_cast<float*>(ctx->step_acc), 2, 0.f, hs));
+    MUSTER_HIP(launch_combine(it, combine_tiles(dims[0], dims[1], dims[2]), hs));
+    MUSTER_HIP(hipMemcpyAsync(reg_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2506,16 +2473,14 @@ muster_status muster_pool2(muster_ctx* h, void* stream, const int dims[3], const
     check_dims(dims, 2);
     NEED(dims[0] % 2 == 0 && dims[1] % 2 == 0 && dims[2] % 2 == 0, "dims must be even");
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     PoolItem it{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.src = src;
     it.dst = dst;
-    const size_t off = sc.add(it);
-    sc.upload();
     const size_t n = (size_t)(dims[0] / 2) * (dims[1] / 2) * (dims[2] / 2);
-    MUSTER_HIP(launch_pool2((const PoolItem*)(sc.dev() + off), 1, elem_tiles(n), sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+    MUSTER_HIP(launch_pool2(it, elem_tiles(n), hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2565,16 +2530,13 @@ muster_status muster_upsample2(muster_ctx* h, void* stream, const int dims[3], c
     check_dims(dims, 2);
     NEED((uint64_t)dims[0] * dims[1] * dims[2] * 8 * 3 < (uint64_t)INT32_MAX, "volume too large");
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     UpItem it{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.src = src;
     it.dst = dst;
-    const size_t off = sc.add(it);
-    sc.upload();
-    MUSTER_HIP(launch_upsample2((const UpItem*)(sc.dev() + off), 1,
-                                up_tiles(dims[0], dims[1], dims[2]), sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+    MUSTER_HIP(launch_upsample2(it, up_tiles(dims[0], dims[1], dims[2]), hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
@@ -2586,16 +2548,13 @@ muster_status muster_upsample2_adjoint(muster_ctx* h, void* stream, const int di
     check_dims(dims, 2);
     NEED((uint64_t)dims[0] * dims[1] * dims[2] * 8 * 3 < (uint64_t)INT32_MAX, "volume too large");
     std::lock_guard<std::mutex> lk(ctx->mu);
-    StepCall sc{ctx, (hipStream_t)stream, {}};
+    hipStream_t hs = (hipStream_t)stream;
     UpItem it{};
     it.D = dims[0]; it.H = dims[1]; it.W = dims[2];
     it.src = src;
     it.dst = dst;
-    const size_t off = sc.add(it);
-    sc.upload();
-    MUSTER_HIP(launch_upsample2_adj((const UpItem*)(sc.dev() + off), 1,
-                                    up_adj_tiles(dims[0], dims[1], dims[2]), sc.s));
-    MUSTER_HIP(hipStreamSynchronize(sc.s));
+    MUSTER_HIP(launch_upsample2_adj(it, up_adj_tiles(dims[0], dims[1], dims[2]), hs));
+    MUSTER_HIP(hipStreamSynchronize(hs));
   });
 }
 
