@@ -708,10 +708,16 @@ int smooth_item_setup(SmoothItem& it, const int dims[3], int axis, float sigma, 
   // LDS floats a tile of L lines needs, and the number of lines on offer
   const int n = dims[axis];
   const int avail = axis == 2 ? dims[0] * dims[1] : dims[2];
-  auto need = [&](int L) { return axis == 2 ? 2 * L * (dims[2] | 1) : n * L; };
+  // staged samples of a line: the outputs' chunks and what they reach beyond
+  const int staged = ceil_div(n, SMOOTH_S) * SMOOTH_S - SMOOTH_S +
+                     ceil_div(2 * r + SMOOTH_S, SMOOTH_S) * SMOOTH_S;
+  auto need = [&](int L) { return axis == 2 ? L * (staged | 1) : staged * L; };
   int L = 64;
-  while (L > 1 && (L / 2 >= avail || need(L) > SMOOTH_LDS_TARGET)) L /= 2;
+  while (L > 1 && (L / 2 >= avail || need(L) > (axis == 2 ? SMOOTH_LDS_ROWS : SMOOTH_LDS_COLS)))
+    L /= 2;
   while (L > 1 && need(L) > SMOOTH_LDS) L /= 2;
+  if (axis == 2)
+    while (L > 1 && L * ceil_div(n, SMOOTH_S) > SMOOTH_XR * BLOCK) L /= 2;
   it.lines = L;
   it.lshift = 0;
   while ((1 << it.lshift) < L) ++it.lshift;
