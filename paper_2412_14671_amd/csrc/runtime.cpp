@@ -246,8 +246,40 @@ uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
 // ---------------------------------------------------------------------------
 // jobs
 // ---------------------------------------------------------------------------
+JobState* Ctx::take_host_state() {
+  {
+    std::lock_guard<std::mutex> lk(host_mu);
+    if (!host_states.empty()) {
+      JobState* h = host_states.back();
+      host_states.pop_back();
+      return h;
+    }
+  }
+  JobState* h = nullptr;
+  MUSTER_HIP(hipHostMalloc((void**)&h, sizeof(JobState), hipHostMallocDefault));
+  return h;
+}
+
+void Ctx::give_host_state(JobState* h) {
+  {
+    std::lock_guard<std::mutex> lk(host_mu);
+    if (host_states.size() < MAX_HOST_STATES) {
+      host_states.reserve(MAX_HOST_STATES);
+      host_states.push_back(h);
+      return;
+    }
+  }
+  (void)hipHostFree(h);
+}
+
+void Ctx::free_host_states() {
+  std::lock_guard<std::mutex> lk(host_mu);
+  for (JobState* h : host_states) (void)hipHostFree(h);
+  host_states.clear();
+}
+
 Job::~Job() {
-  if (host_state) (void)hipHostFree(host_state);
+  if (host_state) ctx->give_host_state(host_state);
 }
 
 float* Job::us_field(int dir, int slot) const {
@@ -374,7 +406,7 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
     off += (size_t)N * J.VI(l);
   }
   J.level_images[L - 1] = const_cast<float*>(J.images_fine);
-  MUSTER_HIP(hipHostMalloc((void**)&J.host_state, sizeof(JobState), hipHostMallocDefault));
+  J.host_state = ctx->take_host_state();
   std::memset(J.host_state, 0, sizeof(JobState));
   J.footprint = J.m_phi.bytes + J.m_m.bytes + J.m_v.bytes + J.m_us.bytes + J.m_deep.bytes +
                 J.m_gpair.bytes + J.m_pp.bytes + J.m_coef.bytes + J.m_img.bytes +
@@ -522,7 +554,6 @@ void job_begin_level(Job& J, int level, hipStream_t s) {
   } else {
     J.sim_tile[level] = choose_sim_tile(ctx, J.idims[level], J.p.window, J.p.metric, s);
   }
-  MUSTER_HIP(hipStreamSynchronize(s));
 }
 
 static void read_state(Job& J, hipStream_t s) {
@@ -535,6 +566,7 @@ void job_final_outputs(Job& J, hipStream_t s) {
   Ctx* ctx = J.ctx;
   std::vector<Job*> one{&J};
   auto plan = build_plan(one, PLAN_FORWARD);
+  StreamGuard flight(s);
   plan->upload(ctx, s);
   plan->run(ctx, s);
   const size_t VI = J.VIc();
@@ -587,6 +619,7 @@ void job_final_outputs(Job& J, hipStream_t s) {
                               hipMemcpyHostToDevice, s));
   }
   MUSTER_HIP(hipStreamSynchronize(s));
+  flight.done();
 }
 
 // ---------------------------------------------------------------------------
@@ -860,6 +893,66 @@ void add_pair_resampling(Builder& b, const std::vector<Job*>& jobs, bool adjoint
   b.add(adjoint ? ST_UPSAMPLE_ADJ : ST_UPSAMPLE, items, tiles, bytes);
 }
 
+// L_L2 and L_ts terms of interval i (Sec. 2.4), on the flows Exp integrates.
+void set_reg_ext(CombineItem& it, const Job& J, int i) {
+  const int N = J.N;
+  const double V = (double)J.Vc();
+  const bool l2 = J.p.alpha_l2 > 0.f;
+  const bool ts = J.p.alpha_ts > 0.f && N >= 3;
+  if (!l2 && !ts) return;
+  double w_self = 0, w_prev = 0, w_next = 0;
+  it.ext = 1;
+  if (l2) {
+    w_self += 2.0 * J.p.alpha_l2 / ((N - 1) * V);
+    it.l2_loss_w = (float)(J.p.alpha_l2 / ((N - 1) * V));
+  }
+  if (ts) {
+    const double c = 2.0 * J.p.alpha_ts / ((N - 2) * V);
+    const double di = J.times[i + 1] - J.times[i];
+    if (i >= 1) {
+      const double dp = J.times[i] - J.times[i - 1];
+      w_self += c / (di * di);
+      w_prev = -c / (dp * di);
+      it.flow_prev = J.flow(i - 1);
+      it.ts_loss_w = (float)(J.p.alpha_ts / ((N - 2) * V));
+      it.inv_dprev = (float)(1.0 / dp);
+      it.inv_dself = (float)(1.0 / di);
+    }
+    if (i <= N - 3) {
+      const double dn = J.times[i + 2] - J.times[i + 1];
+      w_self += c / (di * di);
+      w_next = -c / (di * dn);
+      it.flow_next = J.flow(i + 1);
+    }
+  }
+  it.w_self = (float)w_self;
+  it.w_prev = (float)w_prev;
+  it.w_next = (float)w_next;
+}
+
+// The regularisers' weighted values alone, into the jobs' losses.
+void add_reg_values(Builder& b, const std::vector<Job*>& jobs) {
+  std::vector<CombineItem> items;
+  int tiles = 0;
+  double bytes = 0;
+  for (Job* J : jobs) {
+    const int* d = J->ldims[J->level];
+    for (int i = 0; i < J->N - 1; ++i) {
+      CombineItem it{};
+      it.tile0 = tiles;
+      it.D = d[0]; it.H = d[1]; it.W = d[2];
+      it.flow = J->flow(i);
+      it.loss = &J->js->loss_reg;
+      it.reg_loss_w = (double)J->p.alpha_ss / (J->N - 1);
+      set_reg_ext(it, *J, i);
+      items.push_back(it);
+      tiles += combine_tiles(d[0], d[1], d[2]);
+      bytes += 12.0 * J->Vc();
+    }
+  }
+  b.add(ST_COMBINE, items, tiles, bytes);
+}
+
 void add_forward(Builder& b, const std::vector<Job*>& jobs) {
   int maxK = 0, maxN = 0;
   for (Job* J : jobs) {
@@ -1055,43 +1148,6 @@ void add_sim_stages(Builder& b, const std::vector<Job*>& jobs, StageKind kind) {
     b.add(kind, items, tiles, per * vox, window, kind == ST_SIM_STATS ? metric : 0);
     b.plan->stages.back().shape = shape;
   }
-}
-
-// L_L2 and L_ts terms of interval i (Sec. 2.4), on the flows Exp integrates.
-void set_reg_ext(CombineItem& it, const Job& J, int i) {
-  const int N = J.N;
-  const double V = (double)J.Vc();
-  const bool l2 = J.p.alpha_l2 > 0.f;
-  const bool ts = J.p.alpha_ts > 0.f && N >= 3;
-  if (!l2 && !ts) return;
-  double w_self = 0, w_prev = 0, w_next = 0;
-  it.ext = 1;
-  if (l2) {
-    w_self += 2.0 * J.p.alpha_l2 / ((N - 1) * V);
-    it.l2_loss_w = (float)(J.p.alpha_l2 / ((N - 1) * V));
-  }
-  if (ts) {
-    const double c = 2.0 * J.p.alpha_ts / ((N - 2) * V);
-    const double di = J.times[i + 1] - J.times[i];
-    if (i >= 1) {
-      const double dp = J.times[i] - J.times[i - 1];
-      w_self += c / (di * di);
-      w_prev = -c / (dp * di);
-      it.flow_prev = J.flow(i - 1);
-      it.ts_loss_w = (float)(J.p.alpha_ts / ((N - 2) * V));
-      it.inv_dprev = (float)(1.0 / dp);
-      it.inv_dself = (float)(1.0 / di);
-    }
-    if (i <= N - 3) {
-      const double dn = J.times[i + 2] - J.times[i + 1];
-      w_self += c / (di * di);
-      w_next = -c / (di * dn);
-      it.flow_next = J.flow(i + 1);
-    }
-  }
-  it.w_self = (float)w_self;
-  it.w_prev = (float)w_prev;
-  it.w_next = (float)w_next;
 }
 
 // Deterministic jobs' part of a scatter launch: the job's tiles in it (the
@@ -1370,6 +1426,7 @@ std::unique_ptr<Plan> build_plan(const std::vector<Job*>& jobs, PlanScope scope)
       fail(MUSTER_E_INVALID, "jobs batched together must share window and metric");
   if (scope == PLAN_ITERATION || scope == PLAN_FORWARD || scope == PLAN_LOSS_FWD) add_forward(b, jobs);
   if (scope == PLAN_ITERATION || scope == PLAN_LOSS_FWD) add_sim_stages(b, jobs, ST_SIM_STATS);
+  if (scope == PLAN_LOSS_FWD) add_reg_values(b, jobs);
   if (scope == PLAN_ITERATION || scope == PLAN_LOSS_BWD) add_backward(b, jobs);
   if (scope == PLAN_ITERATION) {
     std::vector<JobState*> st;
@@ -1388,7 +1445,6 @@ void Plan::upload(Ctx* ctx, hipStream_t s) {
   if (blob.empty()) return;
   dev.alloc(ctx, blob.size());
   MUSTER_HIP(hipMemcpyAsync(dev.p, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
-  MUSTER_HIP(hipStreamSynchronize(s));
 }
 
 static int kclass(StageKind k) {
@@ -1524,13 +1580,17 @@ static void run_level(Ctx* ctx, std::vector<Job*>& jobs, int level, hipStream_t 
   const int T = jobs[0]->p.iters[level];
   Range range("muster level %d: %zu jobs, %d steps, %dx%dx%d", level, jobs.size(), T,
               jobs[0]->idims[level][0], jobs[0]->idims[level][1], jobs[0]->idims[level][2]);
+  std::unique_ptr<Plan> plan;
+  StreamGuard flight(s);
   for (Job* J : jobs) job_begin_level(*J, level, s);
   if (T <= 0) return;
-  auto plan = build_plan(jobs, PLAN_ITERATION);
+  plan = build_plan(jobs, PLAN_ITERATION);
   plan->upload(ctx, s);
   MUSTER_HIP(hipStreamSynchronize(s));
   const double t0 = now_seconds();
-  if (use_graph && !ctx->timing) {
+  // capturing and instantiating an iteration costs the host about what
+  // launching it three times does
+  if (use_graph && !ctx->timing && T >= 4) {
     plan->capture(ctx, s);
     for (int t = 0; t < T; ++t) plan->replay(s);
   } else {
@@ -1540,7 +1600,10 @@ static void run_level(Ctx* ctx, std::vector<Job*>& jobs, int level, hipStream_t 
   const double dt = now_seconds() - t0;
   for (Job* J : jobs) J->step_seconds += dt;
   if (ctx->timing) resolve_timing(ctx);
-  for (Job* J : jobs) read_state(*J, s);
+  for (Job* J : jobs)
+    MUSTER_HIP(hipMemcpyAsync(J->host_state, J->js, sizeof(JobState), hipMemcpyDeviceToHost, s));
+  MUSTER_HIP(hipStreamSynchronize(s));
+  flight.done();
 }
 
 static void fill_report(Job& J, double t0, muster_report* rep, hipStream_t s) {
@@ -1610,6 +1673,7 @@ struct HipExecutor : Executor {
     Range range("muster admit job: N %d", j.N);
     auto h = std::make_unique<HipJob>();
     h->job = make_job(ctx, j);
+    StreamGuard flight(s);
     job_begin_level(*h->job, 0, s);
     return h;
   }
@@ -1645,7 +1709,10 @@ struct HipExecutor : Executor {
   }
   int level(JobHandle& h) override { return job_of(h).level; }
   bool nonfinite(JobHandle& h) override { return job_of(h).host_state->nonfinite != 0; }
-  void begin_level(JobHandle& h, int level) override { job_begin_level(job_of(h), level, s); }
+  void begin_level(JobHandle& h, int level) override {
+    StreamGuard flight(s);
+    job_begin_level(job_of(h), level, s);
+  }
   void finish(JobHandle& h, double t_submit, muster_report* rep) override {
     job_final_outputs(job_of(h), s);
     fill_report(job_of(h), t_submit, rep, s);
@@ -1947,6 +2014,7 @@ muster_status muster_ctx_destroy(muster_ctx* h) {
   }
   if (c->step_items) c->arena.release(c->step_items);
   if (c->step_acc) c->arena.release(c->step_acc);
+  c->free_host_states();
   for (auto& t : c->pending) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
@@ -2120,30 +2188,15 @@ muster_status muster_loss_forward(muster_ctx* h, void* stream, int N, const int 
     Job& J = *job;
     J.grad_mode = true;
     J.phi = const_cast<float*>(svf_dev);
-    job_begin_level(J, 0, s);
     std::vector<Job*> one{&J};
-    auto plan = build_plan(one, PLAN_LOSS_FWD);
+    std::unique_ptr<Plan> plan;
+    StreamGuard flight(s);
+    job_begin_level(J, 0, s);
+    plan = build_plan(one, PLAN_LOSS_FWD);
     plan->upload(ctx, s);
     plan->run(ctx, s);
-    const GridDims fd{J.ldims[0][0], J.ldims[0][1], J.ldims[0][2]};  // the flow grid
-    {
-      // the regularisers' values alone
-      std::vector<CombineItem> items;
-      int tiles = 0;
-      for (int i = 0; i < N - 1; ++i) {
-        CombineItem it{};
-        it.tile0 = tiles;
-        it.D = fd.D; it.H = fd.H; it.W = fd.W;
-        it.flow = J.flow(i);
-        it.loss = &J.js->loss_reg;
-        it.reg_loss_w = (double)params->alpha_ss / (N - 1);
-        set_reg_ext(it, J, i);
-        items.push_back(it);
-        tiles += combine_tiles(fd.D, fd.H, fd.W);
-      }
-      run_items(ctx, items, tiles, s, launch_combine);
-    }
     read_state(J, s);
+    flight.done();
     if (ctx->timing) resolve_timing(ctx);
     *loss_host = J.host_state->loss_sim + J.host_state->loss_reg;
     auto* sv = new muster_saved;
@@ -2167,9 +2220,11 @@ muster_status muster_loss_backward(muster_ctx* h, void* stream, muster_saved* sa
     J.grad_alias = overlap(grad_svf_dev, J.phi, (size_t)(J.N - 1) * 3 * J.Vc());
     std::vector<Job*> one{&J};
     auto plan = build_plan(one, PLAN_LOSS_BWD);
+    StreamGuard flight(s);
     plan->upload(ctx, s);
     plan->run(ctx, s);
     MUSTER_HIP(hipStreamSynchronize(s));
+    flight.done();
     if (ctx->timing) resolve_timing(ctx);
     saved->used = true;
   });
@@ -2681,6 +2736,7 @@ muster_status muster_ctx_trim(muster_ctx* h, uint64_t* released) {
     NEED(ctx, "ctx is NULL");
     MUSTER_HIP(hipSetDevice(ctx->device));
     const uint64_t b = ctx->arena.trim();
+    ctx->free_host_states();
     if (released) *released = b;
   });
 }

@@ -93,6 +93,14 @@ struct Ctx {
   std::vector<hipEvent_t> event_pool;
   std::mutex timing_mu;
   std::mutex mu;                     // serialises API calls that use ws
+  // Pinned job states kept for the next job (allocating and freeing one costs
+  // 95 us), at most MAX_HOST_STATES; given back by trim and with the context.
+  static constexpr size_t MAX_HOST_STATES = 64;
+  std::vector<JobState*> host_states;
+  std::mutex host_mu;
+  JobState* take_host_state();
+  void give_host_state(JobState* h);
+  void free_host_states();
   void* step_items = nullptr;        // device buffer for single-step item tables
   size_t step_items_bytes = 0;
   double* step_acc = nullptr;        // device doubles for single-step results
@@ -106,6 +114,20 @@ struct Ctx {
   std::string tune_path;             // optional on-disk cache (MUSTER_TUNE_CACHE)
   std::mutex tune_mu;
   Ctx(uint64_t budget, int device) : arena(budget, device) {}
+};
+
+// Waits for the stream when a scope is left before done(): work in flight must
+// not outlive the memory that the scope's owners give back.
+struct StreamGuard {
+  hipStream_t s;
+  bool armed = true;
+  explicit StreamGuard(hipStream_t st) : s(st) {}
+  StreamGuard(const StreamGuard&) = delete;
+  StreamGuard& operator=(const StreamGuard&) = delete;
+  ~StreamGuard() {
+    if (armed) (void)hipStreamSynchronize(s);
+  }
+  void done() { armed = false; }
 };
 
 // Device allocation owned through the context's arena.
@@ -224,7 +246,9 @@ uint64_t job_footprint(int N, const int dims[3], const muster_params& p);
 void validate_params(const muster_params& p);
 void validate_problem(int N, const int dims[3], const muster_params& p, const double* times);
 std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& j);
-void job_begin_level(Job& job, int level, hipStream_t s);   // pyramid, init/upsample, zero state
+// Pyramid, init / upsample, zero state.  Enqueued only: the caller waits for the
+// stream before the job may end.
+void job_begin_level(Job& job, int level, hipStream_t s);
 void job_final_outputs(Job& job, hipStream_t s);           // final forward + copies to the caller
 // The window-statistics tiling for one problem shape under the context's
 // mode; autotuning times every candidate once on scratch data on stream s.
@@ -257,7 +281,7 @@ struct Plan {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   ~Plan();
-  void upload(Ctx* ctx, hipStream_t s);
+  void upload(Ctx* ctx, hipStream_t s);         // enqueued: the blob stays until the plan ends
   void run(Ctx* ctx, hipStream_t s);            // eager
   void capture(Ctx* ctx, hipStream_t s);
   void replay(hipStream_t s);
