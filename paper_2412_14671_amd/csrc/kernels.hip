@@ -20,6 +20,7 @@
 #include <mutex>
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <climits>
 #include <cmath>
 
@@ -1184,10 +1185,13 @@ __global__ __launch_bounds__(BLOCK) void k_exp_far(const Items items, int n_tile
 // ---------------------------------------------------------------------------
 // The gradient of each SVF from the G_0 of its forward and backward
 // directions, and the regularisers (Eq. reg_sum): out = gmul (gf + gb +
-// the regularisers' gradients), and their weighted values added to *loss.
+// the regularisers' gradients), and their weighted values added to loss.
 // Blocks of CT_Y x CT_X columns walk CT_Z planes; the neighbours along z stay
 // in registers and those in the plane come from cache, so the field is read
 // from memory once and the kernel moves 12 bytes per field named in the item.
+// Bound by latency: few planes per thread, many blocks, and the values' sums in
+// slots (LOSS_SLOTS).  Three fields of 160x192x160: the values alone 103 -> 74
+// us, with the gradient of two directions 170 -> 154 us.
 // ---------------------------------------------------------------------------
 template <class Items>
 __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int n_tiles) {
@@ -1205,7 +1209,8 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int 
   const cgfloat* __restrict__ gb = gp(it.gb);
   const cgfloat* __restrict__ f = gp(it.flow);
   gfloat* __restrict__ out = gp(it.out);
-  const bool reg = it.reg_w != 0.f || it.reg_loss_w != 0.0;  // uniform
+  const bool reg = it.reg_w != 0.f || it.loss_w[0] != 0.0;  // uniform
+  const bool grad = it.out != nullptr;  // the value alone takes forward differences only
   const float inv_mz = 1.f / (float)((D - 1) * H * W), inv_my = 1.f / (float)(D * (H - 1) * W),
               inv_mx = 1.f / (float)(D * H * (W - 1));
   double sz = 0.0, sy = 0.0, sx = 0.0, ext = 0.0;
@@ -1216,7 +1221,7 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int 
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         fc[c] = ldo(f + c * V, p);
-        if (z0 > 0) fm[c] = ldo(f + c * V, p - HW);
+        if (grad && z0 > 0) fm[c] = ldo(f + c * V, p - HW);
       }
     }
     for (int z = z0; z < z1; ++z, p += HW) {
@@ -1235,9 +1240,9 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int 
         for (int c = 0; c < 3; ++c) {
           const cgfloat* __restrict__ q = f + c * V;
           fp[c] = z + 1 < D ? ldo(q, p + HW) : 0.f;
-          ym[c] = y > 0 ? ldo(q, p - W) : 0.f;
+          ym[c] = grad && y > 0 ? ldo(q, p - W) : 0.f;
           yp[c] = y + 1 < H ? ldo(q, p + W) : 0.f;
-          xm[c] = x > 0 ? ldo(q, p - 1) : 0.f;
+          xm[c] = grad && x > 0 ? ldo(q, p - 1) : 0.f;
           xp[c] = x + 1 < W ? ldo(q, p + 1) : 0.f;
         }
         // squares summed in float over the components of one voxel, in double
@@ -1285,10 +1290,9 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int 
     }
   }
   if (it.loss && (reg || it.ext)) {
-    const double val = sz / ((double)(D - 1) * H * W) + sy / ((double)D * (H - 1) * W) +
-                       sx / ((double)D * H * (W - 1));
-    const double tot = block_sum<CT_Y * CT_X>(it.reg_loss_w * val + ext, red);
-    if (threadIdx.x == 0) unsafeAtomicAdd(it.loss, tot);
+    const double tot = block_sum<CT_Y * CT_X>(it.loss_w[0] * sz + it.loss_w[1] * sy + it.loss_w[2] * sx + ext, red);
+    if (threadIdx.x == 0)
+      unsafeAtomicAdd(it.loss + (blockIdx.x % LOSS_SLOTS) * LOSS_STRIDE, tot);
   }
 }
 
@@ -2201,12 +2205,12 @@ __global__ void k_finish(JobState* const* __restrict__ states, int n_jobs) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_jobs) return;
   JobState* js = states[i];
-  const double L = js->loss_sim + js->loss_reg;
+  const double L = js->loss_sim + slot_sum(js->loss_reg);
   const int h = js->hist_base + js->t;
   if (js->history && h >= 0 && h < js->hist_len) js->history[h] = L;
   if (!isfinite(L)) js->nonfinite = 1;
   js->loss_sim = 0.0;
-  js->loss_reg = 0.0;
+  for (int k = 0; k < LOSS_SLOTS; ++k) js->loss_reg[k * LOSS_STRIDE] = 0.0;
   for (int k = 0; k < js->n_flags; ++k) js->flags[k] = 0;
   js->t += 1;
 }
@@ -2298,7 +2302,10 @@ __device__ __forceinline__ float up_weight(int f, int c, int n) {
 // of UA_TZ x UA_TY x UA_TX coarse voxels (2t + 2 fine samples per axis) in
 // LDS, one component at a time, and sums along x, then y, then z, with the
 // 4 weights per coarse index of each axis computed once per block: every fine
-// sample is read from HBM once and the 64-tap gather becomes 3 x 4 taps.
+// sample is read from HBM once and the 64-tap gather becomes 3 x 4 taps.  A
+// thread stages whole columns of the region (one offset each, where every
+// sample's position was worked out from its index): 96x128x112 coarse voxels
+// 76 -> 60 us, against 149 MB moved.
 template <class Items>
 __global__ __launch_bounds__(BLOCK) void k_upsample2_adj(const Items items, int n_tiles) {
   constexpr int FZ = 2 * UA_TZ + 2, FY = 2 * UA_TY + 2, FX = 2 * UA_TX + 2;
@@ -2336,22 +2343,32 @@ __global__ __launch_bounds__(BLOCK) void k_upsample2_adj(const Items items, int 
   }
   const cgfloat* __restrict__ g = gp(it.src);
   gfloat* __restrict__ out = gp(it.dst);
-  for (int c = 0; c < 3; ++c) {
-    // UL loads in flight per thread before they land in LDS
-    constexpr int UL = 8;
-    for (int i0 = threadIdx.x; i0 < FN; i0 += BLOCK * UL) {
-      float v[UL];
+  // the columns of the fine region that this thread stages
+  constexpr int NC = (FY * FX + BLOCK - 1) / BLOCK;
+  uint32_t off[NC];
+  bool col[NC], in[NC];
 #pragma unroll
-      for (int u = 0; u < UL; ++u) {
-        const int i = i0 + u * BLOCK;
-        const int lz = i / (FY * FX), r = i - lz * (FY * FX), ly = r / FX, lx = r - ly * FX;
-        const int fz = fz0 + lz, fy = fy0 + ly, fx = fx0 + lx;
-        const bool in = i < FN && fz >= 0 && fz < D2 && fy >= 0 && fy < H2 && fx >= 0 && fx < W2;
-        v[u] = in ? g[c * n2 + (fz * H2 + fy) * W2 + fx] : 0.f;
+  for (int k = 0; k < NC; ++k) {
+    const int q = threadIdx.x + k * BLOCK, ly = q / FX, lx = q - ly * FX;
+    const int fy = fy0 + ly, fx = fx0 + lx;
+    col[k] = q < FY * FX;
+    in[k] = col[k] && fy >= 0 && fy < H2 && fx >= 0 && fx < W2;
+    off[k] = in[k] ? (uint32_t)(fy * W2 + fx) : 0u;
+  }
+  for (int c = 0; c < 3; ++c) {
+    // a column of the region per thread and round, all its planes in flight
+    // before they land in LDS
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      if (!col[k]) continue;
+      float v[FZ];
+#pragma unroll
+      for (int lz = 0; lz < FZ; ++lz) {
+        const int fz = fz0 + lz;
+        v[lz] = in[k] && fz >= 0 && fz < D2 ? ldo(g + c * n2, (uint32_t)(fz * (H2 * W2)) + off[k]) : 0.f;
       }
 #pragma unroll
-      for (int u = 0; u < UL; ++u)
-        if (i0 + u * BLOCK < FN) fine[i0 + u * BLOCK] = v[u];
+      for (int lz = 0; lz < FZ; ++lz) fine[lz * (FY * FX) + threadIdx.x + k * BLOCK] = v[lz];
     }
     __syncthreads();
     for (int i = threadIdx.x; i < S1; i += BLOCK) {
@@ -2451,7 +2468,7 @@ static hipError_t compose_fwd_(const Items& items, int n_tiles, hipStream_t s) {
 template <bool DETMAX, class Items>
 static hipError_t exp_far_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  const int group = n_tiles < 4096 ? 1 : n_tiles < 16384 ? 4 : 8;
+  const int group = std::min(8, std::max(1, n_tiles / 512));
   MUSTER_LAUNCH((k_exp_far<DETMAX, Items>), dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items,
                 n_tiles, group);
   return hipGetLastError();

@@ -23,6 +23,15 @@ namespace muster {
 // the float one.  One slot per such launch of an iteration.
 constexpr int DET_SLOTS = 96;
 
+// Blocks that add into one double follow each other at about 13 ns, so the
+// regularisers' sums are spread over slots on lines of their own.
+constexpr int LOSS_SLOTS = 16, LOSS_STRIDE = 16;
+inline __host__ __device__ double slot_sum(const double* s) {
+  double v = 0.0;
+  for (int k = 0; k < LOSS_SLOTS; ++k) v += s[k * LOSS_STRIDE];
+  return v;
+}
+
 // Per-job device state: optimiser step counter and schedule, loss
 // accumulators and the loss history.  Lives in device memory so that a
 // captured iteration can be replayed without host involvement.
@@ -33,7 +42,7 @@ struct JobState {
   int nonfinite;    // set once the loss is not finite
   float lr0, b1, b2, eps;
   double loss_sim;  // accumulated over the current iteration
-  double loss_reg;  // weighted regularisers
+  double loss_reg[LOSS_SLOTS * LOSS_STRIDE];  // weighted regularisers, in slots
   double* history;  // loss per step (device), length hist_len
   int hist_len;
   int* flags;       // per Exp-backward step: its fixed-point field was added to (deterministic
@@ -230,7 +239,7 @@ struct AdamItem {
 // The gradient of an SVF: out = gmul * (gf + gb + the regularisers'
 // gradients), gf and gb the (scaled, signed) G_0 of its two directions, each
 // of them and out NULL where not wanted; the regularisers' values are added
-// to *loss (NULL: not wanted).
+// to loss (NULL: not wanted).
 struct CombineItem {
   int tile0;
   int D, H, W;
@@ -238,8 +247,8 @@ struct CombineItem {
   const float* gb;
   float* out;
   const float* flow;   // the flow the regularisers act on
-  double* loss;
-  double reg_loss_w;   // weight of the L_ss value
+  double* loss;        // LOSS_SLOTS slots
+  double loss_w[3];    // weights of the L_ss value's squares along z, y, x, the counts divided out
   float gmul;
   float reg_w;         // weight of the L_ss gradient
   // L_L2 and L_ts: the gradient gains w_self f_i + w_prev f_{i-1} + w_next
@@ -251,6 +260,11 @@ struct CombineItem {
   float l2_loss_w, ts_loss_w, inv_dprev, inv_dself;
   const float* flow_prev;
   const float* flow_next;
+  void set_loss_weight(double w) {
+    loss_w[0] = w / ((double)(D - 1) * H * W);
+    loss_w[1] = w / ((double)D * (H - 1) * W);
+    loss_w[2] = w / ((double)D * H * (W - 1));
+  }
 };
 
 // One separable pass of the periodic Gaussian smoothing along one axis, for
@@ -325,7 +339,7 @@ constexpr int MT_Y = 8, MT_X = 32;
 // and 56 registers).
 constexpr int EXP_BWD_SLOTS = 1280, EXP_FWD_SLOTS = 2048;
 // Tiles of the combination of the SVF gradients.
-constexpr int CT_Z = 8, CT_Y = 8, CT_X = 32;
+constexpr int CT_Z = 4, CT_Y = 8, CT_X = 32;
 // Tiles of the windowed-statistics kernels: TY x TX columns, z chunks.
 // Tile shapes (centres in y x x) of the window-statistics kernels; the block
 // has one thread per centre.

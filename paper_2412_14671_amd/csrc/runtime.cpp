@@ -942,8 +942,8 @@ void add_reg_values(Builder& b, const std::vector<Job*>& jobs) {
       it.tile0 = tiles;
       it.D = d[0]; it.H = d[1]; it.W = d[2];
       it.flow = J->flow(i);
-      it.loss = &J->js->loss_reg;
-      it.reg_loss_w = (double)J->p.alpha_ss / (J->N - 1);
+      it.loss = J->js->loss_reg;
+      it.set_loss_weight((double)J->p.alpha_ss / (J->N - 1));
       set_reg_ext(it, *J, i);
       items.push_back(it);
       tiles += combine_tiles(d[0], d[1], d[2]);
@@ -1367,9 +1367,9 @@ void add_backward(Builder& b, const std::vector<Job*>& jobs) {
           it.gmul = J->grad_scale;
         }
         it.flow = J->flow(i);
-        it.loss = &J->js->loss_reg;
+        it.loss = J->js->loss_reg;
         it.reg_w = J->p.alpha_ss / (float)(J->N - 1);
-        it.reg_loss_w = it.reg_w;
+        it.set_loss_weight(it.reg_w);
         set_reg_ext(it, *J, i);
         items.push_back(it);
         tiles += combine_tiles(d[0], d[1], d[2]);
@@ -1997,7 +1997,7 @@ muster_status muster_ctx_create(int device, uint64_t hbm_budget, muster_ctx** ou
     MUSTER_HIP(hipStreamCreateWithFlags(&c->ws, hipStreamNonBlocking));
     c->step_items_bytes = 1 << 20;
     c->step_items = c->arena.try_alloc(c->step_items_bytes);
-    c->step_acc = (double*)c->arena.try_alloc(64 * sizeof(double));
+    c->step_acc = (double*)c->arena.try_alloc(STEP_DOUBLES * sizeof(double));
     NEED(c->step_items && c->step_acc, "could not allocate context buffers");
     *out = new muster_ctx{c.release()};
   });
@@ -2198,7 +2198,7 @@ muster_status muster_loss_forward(muster_ctx* h, void* stream, int N, const int 
     read_state(J, s);
     flight.done();
     if (ctx->timing) resolve_timing(ctx);
-    *loss_host = J.host_state->loss_sim + J.host_state->loss_reg;
+    *loss_host = J.host_state->loss_sim + slot_sum(J.host_state->loss_reg);
     auto* sv = new muster_saved;
     sv->ctx = h;
     sv->job = std::move(job);
@@ -2518,11 +2518,13 @@ muster_status muster_reg(muster_ctx* h, void* stream, const int dims[3], const f
     it.out = grad;
     it.gmul = it.reg_w = 1.f;
     it.loss = ctx->step_acc;
-    it.reg_loss_w = 1.0;
-    MUSTER_HIP(launch_fill(reinterpret_cast<float*>(ctx->step_acc), 2, 0.f, hs));
+    it.set_loss_weight(1.0);
+    MUSTER_HIP(launch_fill(reinterpret_cast<float*>(ctx->step_acc), 2 * STEP_DOUBLES, 0.f, hs));
     MUSTER_HIP(launch_combine(it, combine_tiles(dims[0], dims[1], dims[2]), hs));
-    MUSTER_HIP(hipMemcpyAsync(reg_host, ctx->step_acc, sizeof(double), hipMemcpyDeviceToHost, hs));
+    double sums[STEP_DOUBLES];
+    MUSTER_HIP(hipMemcpyAsync(sums, ctx->step_acc, sizeof sums, hipMemcpyDeviceToHost, hs));
     MUSTER_HIP(hipStreamSynchronize(hs));
+    *reg_host = slot_sum(sums);
   });
 }
 
@@ -2644,7 +2646,7 @@ muster_status muster_field_metrics(muster_ctx* h, void* stream, const int dims[3
     std::lock_guard<std::mutex> lk(ctx->mu);
     hipStream_t s = (hipStream_t)stream;
     const int V = dims[0] * dims[1] * dims[2];
-    double* acc = ctx->step_acc;  // 64 doubles
+    double* acc = ctx->step_acc;  // 27 of its doubles
     MUSTER_HIP(hipMemsetAsync(acc, 0, 27 * sizeof(double), s));
     MUSTER_HIP(launch_field_stats(V, ref, est, roi, acc, s));
     double t[27];

@@ -63,6 +63,9 @@ struct KernelStats {
   double bytes[MUSTER_K_COUNT] = {};
 };
 
+// Device doubles of the context for the sums of single-step calls.
+constexpr int STEP_DOUBLES = LOSS_SLOTS * LOSS_STRIDE;
+
 struct Server;
 
 // Tile choice of the window-statistics kernels (shape index into
