@@ -442,12 +442,13 @@ __device__ __forceinline__ ScatterBox scatter_box(int (&lo)[3], int (&hi)[3], fl
 // Gathers from a box staged in LDS.  The block reduces the bounding box of
 // the cells its voxels sample (the reduction of the scatters), loads that box
 // of the three component planes straight into LDS (coalesced loads that do
-// not pass through registers), and reads the 8 corners of each cell there.  A few wide row loads per cell then replace
-// the scattered corner loads of every voxel, which otherwise keep the L1 and
-// texture path saturated.  The values and the arithmetic are those of
-// sample_cells, so the result is bit-identical; a box larger than
-// GATHER_CELLS falls back to sample_cells.  box: LDS of 3 * GATHER_CELLS
-// floats.  Every thread of the block must call this.
+// not pass through registers), and reads the 8 corners of each cell there.  A
+// few wide row loads per cell then replace the scattered corner loads of every
+// voxel, which otherwise keep the L1 and texture path saturated.  The values
+// and the arithmetic are those of sample_cells, so the result is
+// bit-identical; a box larger than GATHER_CELLS falls back to sample_cells.
+// box: LDS of 3 * GATHER_CELLS floats.  Every thread of the block must call
+// this.
 //
 // 2560 cells (30 KB of LDS) let five blocks share a CU, and the kernels that
 // stage a box are held to five waves per SIMD (at most 102 VGPRs, no spill):
@@ -946,8 +947,8 @@ __global__ __launch_bounds__(MT_NT) void k_exp_fwd(const Items items, int n_tile
 // Bound by vector issue: about 330 instructions per voxel, where the exchange
 // of scatter boxes in LDS that this replaced took 512 and moved 60 bytes per
 // voxel against 43 (the columns' halo included).  160x192x160, K 7, the whole
-// adjoint with its forward steps: 975 -> 672 us, and the error against 64 bits
-// 1.2e-5 -> 1.3e-7.  8 x 32 columns: whole 128-byte lines per row and no bank
+// adjoint with its forward steps: 975 -> 672 us (584 with those marching as
+// well), and the error against 64 bits 1.2e-5 -> 1.2e-7.  8 x 32 columns: whole 128-byte lines per row and no bank
 // conflicts between a wave's rows; six 160x192x160 fields at once take 284 us,
 // with 16 x 16 columns 361, with 16 x 32 300, with 8 x 16 403, with 4 x 64 324.
 // ---------------------------------------------------------------------------
@@ -1120,16 +1121,17 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tile
 
 // What the voxels that are not near spread, added into the field that
 // k_exp_bwd has written, over the point tiles it marked.  A block looks at
-// `group` marks with one load and ends there when none is set, which is
-// the usual case: displacements reach a voxel only in the last squarings of a
-// large deformation.  The marks are cleared once read.  DETMAX: the
+// `group` marks, a grid apart, with one load and ends there when none is set,
+// which is the usual case: displacements reach a voxel only in the last
+// squarings of a large deformation, and then in neighbouring tiles, which so
+// fall to different blocks.  The marks are cleared once read.  DETMAX: the
 // deterministic mode's reduce-only pass (no writes but the job's slot).
 template <bool DETMAX, class Items>
 __global__ __launch_bounds__(BLOCK) void k_exp_far(const Items items, int n_tiles, int group) {
   __shared__ __align__(16) int acc[DETMAX ? 4 : 3 * SCATTER_CELLS];
   __shared__ int sred[8 * (BLOCK / 64)];
   const int lane = threadIdx.x & 63;
-  const int mine = blockIdx.x * group + lane;
+  const int mine = blockIdx.x + lane * gridDim.x;
   int mark = 0;
   if (lane < group && mine < n_tiles) {
     const ExpBwdItem& m = items.at(mine);
@@ -1139,7 +1141,7 @@ __global__ __launch_bounds__(BLOCK) void k_exp_far(const Items items, int n_tile
   if (!todo) return;
   __syncthreads();  // every wave has read the marks
   while (todo) {
-    const int tile = blockIdx.x * group + __builtin_ctzll(todo);
+    const int tile = blockIdx.x + __builtin_ctzll(todo) * gridDim.x;
     todo &= todo - 1;
     const ExpBwdItem it = items.at(tile);
     const int D = it.D, H = it.H, W = it.W, V = D * H * W;
@@ -2462,13 +2464,15 @@ static hipError_t compose_fwd_(const Items& items, int n_tiles, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Marks per block of k_exp_far: blocks that look at more end sooner where none
-// is set (28800 marks in eights: 6 us), but take their marked tiles one after
-// another.
+// Marks per block of k_exp_far: a launch is about as many blocks as walk at
+// once (100 VGPRs: four per CU), up to the 64 marks that one load of a wave
+// holds.  With eight marks per block, side by side, 28800 unset ones took 6.9
+// us against 4.9, half a million 142 against some 60, and the adjoint of a
+// 160x192x160 field of up to 8 voxels 971 us against 949.
 template <bool DETMAX, class Items>
 static hipError_t exp_far_(const Items& items, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  const int group = std::min(8, std::max(1, n_tiles / 512));
+  const int group = std::min(64, std::max(1, n_tiles / 1024));
   MUSTER_LAUNCH((k_exp_far<DETMAX, Items>), dim3(ceil_div(n_tiles, group)), dim3(BLOCK), 0, s, items,
                 n_tiles, group);
   return hipGetLastError();
