@@ -151,6 +151,24 @@ __device__ __forceinline__ void sto(gfloat* plane, uint32_t i, float v) {
   *(GLOBAL float*)((GLOBAL char*)plane + (i << 2)) = v;
 }
 
+// The window statistics' coefficients alpha, beta, gamma of one voxel, at voxel
+// i of a plane whose base is uniform across the wave: one 12-byte access at a
+// 32-bit offset (a plane has fewer than 2^28 voxels, the grid at least three
+// planes).
+struct Coef {
+  float a, b, c;
+};
+__device__ __forceinline__ Coef ldo_coef(const GLOBAL Coef* plane, uint32_t i) {
+  const cgfloat* p = (const cgfloat*)((const GLOBAL char*)plane + i * (uint32_t)sizeof(Coef));
+  return {p[0], p[1], p[2]};
+}
+__device__ __forceinline__ void sto_coef(GLOBAL Coef* plane, uint32_t i, Coef v) {
+  gfloat* p = (gfloat*)((GLOBAL char*)plane + i * (uint32_t)sizeof(Coef));
+  p[0] = v.a;
+  p[1] = v.b;
+  p[2] = v.c;
+}
+
 // The 8 corners of a cell.  Corner order: bit 0 = x+1, bit 1 = y+1,
 // bit 2 = z+1; the x pairs are adjacent in memory and come in one load.
 __device__ __forceinline__ void load8(const cgfloat* __restrict__ f, int base, int sy, int sz,
@@ -1487,10 +1505,11 @@ __global__ void k_det_clear(JobState* const* __restrict__ states, int n_jobs) {
 //
 // The stages work on several slices at once (loading n + 3, storing n + 2,
 // summing n + 1 over x, and n over y and z) in two buffers, with one barrier per
-// slice.  Bound by memory: 12 pairs of 160x192x160 at w 7 move 3.0 GB
-// (coefficients with their halo, field, images, gradient) at 4.7 TB/s: 1040 ->
-// 640 us against z-sums of every patch column in a moving ring first, at three
-// barriers per slice.
+// slice.  Bound by memory (coefficients with their halo, field, images,
+// gradient): 12 pairs of 160x192x160 at w 7 took 1040 us with z-sums of every
+// patch column in a moving ring first, at three barriers per slice, and 660 like
+// this.  The coefficients of a voxel lie together, so that a patch row of 38
+// voxels touches five 128-byte lines where three planes made it nine: 582 us.
 // ---------------------------------------------------------------------------
 struct STile {
   int z0, z1, y0, x0;
@@ -1648,7 +1667,7 @@ __global__ __launch_bounds__(TY * TX) void k_sim_stats(const Items items, int n_
   if (z0 >= z1) return;
   const cgfloat* __restrict__ F = gp(it.F);
   const cgfloat* __restrict__ M = gp(it.M);
-  const Planes<gfloat> cf(gp(it.coef), V);
+  GLOBAL Coef* const cf = (GLOBAL Coef*)it.coef;
   const bool coef = it.coef != nullptr;
   const int pm = (min((c0 + c1) / 2, D - 1) * H + min(tc.y0 + TY / 2, H - 1)) * W +
                  min(tc.x0 + TX / 2, W - 1);
@@ -1826,10 +1845,7 @@ __global__ __launch_bounds__(TY * TX) void k_sim_stats(const Items items, int n_
         ga = ac * inv_n;
       }
       if (coef) {
-        const uint32_t p = (uint32_t)((zcen * H + y) * W + x);
-        sto(cf.c[0], p, al);
-        sto(cf.c[1], p, be);
-        sto(cf.c[2], p, ga);
+        sto_coef(cf + (size_t)zcen * HW, (uint32_t)(y * W + x), Coef{al, be, ga});
       }
     }
     if (zvalid) __syncthreads();  // zs is written again next
@@ -1861,7 +1877,8 @@ __global__ __launch_bounds__(TY * TX) void k_sim_grad(const Items items, int n_t
   const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, it.zg);
   const cgfloat* __restrict__ F = gp(it.F);
   const cgfloat* __restrict__ I = gp(it.I);
-  const Planes<const cgfloat> Up(gp(it.U), V), cf(gp((const float*)it.coef), V);
+  const Planes<const cgfloat> Up(gp(it.U), V);
+  const GLOBAL Coef* const cf = (const GLOBAL Coef*)it.coef;
   const Planes<gfloat> gU(gp(it.gU), V);
   const float inv_nr = (float)it.inv_nr;
   const int tid = threadIdx.x, ty = tid / TX, tx = tid % TX;
@@ -1881,12 +1898,14 @@ __global__ __launch_bounds__(TY * TX) void k_sim_grad(const Items items, int n_t
 #pragma unroll
   for (int k = 0; k < NS; ++k) cv[0][k] = cv[1][k] = cv[2][k] = 0.f;
   auto load = [&](int z) {
-    const uint32_t base = (uint32_t)(min(max(z, 0), D - 1) * HW);
+    const GLOBAL Coef* const plane = cf + (size_t)min(max(z, 0), D - 1) * HW;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
       if (!sin[k]) continue;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) cv[q][k] = ldo(cf.c[q], base + soff[k]);
+      const Coef v = ldo_coef(plane, soff[k]);
+      cv[0][k] = v.a;
+      cv[1][k] = v.b;
+      cv[2][k] = v.c;
     }
   };
   auto put = [&](int b) {

@@ -197,7 +197,7 @@ struct SimItem {
   const float* U;
   float* M;      // [V]: I warped by U (and the rigid adjustment), written by k_warp and read
                  // by k_sim_stats; may be the first plane of gU, which k_sim_grad overwrites
-  float* coef;   // [3][V]: alpha, beta, gamma per window centre (may be null in sim_stats)
+  float* coef;   // [V][3]: alpha, beta, gamma per window centre (may be null in sim_stats)
   float* gU;     // [3][V]: dSim/dU, written by sim_grad
   double inv_nr; // 1 / number of windows
   JobState* js;  // loss accumulator (may be null)
