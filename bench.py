@@ -262,6 +262,14 @@ def kernels_sha256():
     return h.hexdigest()
 
 
+def exp_bwd_blocks(N, dims):
+    """Blocks of a `k_exp_bwd` launch for one subject: columns of 8 x 32 voxels in chunks of 32
+    planes for each of the 2 (N - 1) directions.  (Launches of few blocks take shorter chunks;
+    the counter summaries then hold no such grid.)"""
+    D, H, W = dims
+    return 2 * (N - 1) * (-(-D // 32)) * (-(-H // 8)) * (-(-W // 32))
+
+
 def traffic_per_launch(path, kernel, launch_grids):
     """HBM bytes per launch of `kernel` (e.g. "k_exp_bwd") from the committed
     counter summary, weighted like the timed launches ({grid in blocks:
@@ -441,8 +449,7 @@ def bench_headline(args, ctx, dev, torch, synth, MusterParams):
     value = per_step * K / dt
     # exp_bwd launches of one batched step: one per squaring (K = 7), each over
     # every direction of every subject
-    grid = sum(2 * (s.images.shape[0] - 1) * (-(-s.images.shape[1] // 8)) * (-(-s.images.shape[2] // 8))
-               * (-(-s.images.shape[3] // 16)) for s in subjects)
+    grid = sum(exp_bwd_blocks(s.images.shape[0], s.images.shape[1:]) for s in subjects)
     traffic = {"exp_bwd": traffic_per_launch(args.traffic, "k_exp_bwd", {grid: 7 * K})}
     _, roof = roofline_from_stats(stats_timed, traffic, stats_timed)
     if roof is not None:
@@ -668,11 +675,11 @@ def bench_register(args, ctx, dev, torch, synth, MusterParams):
     roi = s.roi.cpu().numpy()
     svf_np = svf.cpu().numpy()
     true_np = s.svf_true.cpu().numpy()
-    # exp_bwd launches per level: K per iteration, tiles 2(N-1) x point tiles (8x8x16)
+    # exp_bwd launches per level: K per iteration
     grids = {}
     for l in range(L):
         d = [x // 2 ** (L - 1 - l) for x in shape]
-        g = 2 * (N - 1) * (-(-d[0] // 8)) * (-(-d[1] // 8)) * (-(-d[2] // 16))
+        g = exp_bwd_blocks(N, d)
         grids[g] = grids.get(g, 0) + 7 * iters[l] * args.steps
     traffic = {"exp_bwd": traffic_per_launch(args.traffic, "k_exp_bwd", grids)}
     kname, roof = roofline_from_stats(stats, traffic, stats_timed)

@@ -629,7 +629,7 @@ namespace {
 
 // Algorithmic bytes per voxel (the unique bytes each step must move).
 constexpr double B_EXP_FWD = 24, B_COMPOSE_FWD = 36, B_SIM_STATS = 20, B_SIM_GRAD = 32,
-                 B_COMPOSE_BWD = 84, B_EXP_BWD = 60, B_ADAM = 96, B_SMOOTH = 24, B_WARP = 20,
+                 B_COMPOSE_BWD = 84, B_EXP_BWD = 36, B_ADAM = 96, B_SMOOTH = 24, B_WARP = 20,
                  B_COMBINE = 36;
 
 struct Builder {
