@@ -82,7 +82,8 @@ typedef struct muster_params {
   float beta1, beta2, eps;         /* Adam constants                              */
   int exp_mode;                    /* MUSTER_EXP_STORE or _RECOMPUTE: keep the K
                                       squaring fields for the backward pass, or
-                                      recompute them from phi                     */
+                                      the last one and a ring of up to four others,
+                                      formed anew from phi as the pass goes back  */
   int use_graph;                   /* 1: replay each level's iteration as a
                                       captured hipGraph; 0: eager launches        */
   float smooth_sigma;              /* Gaussian smoothing of the flow before Exp
