@@ -2486,7 +2486,7 @@ static hipError_t compose_fwd_(const Items& items, int n_tiles, hipStream_t s) {
 // Marks per block of k_exp_far: a launch is about as many blocks as walk at
 // once (100 VGPRs: four per CU), up to the 64 marks that one load of a wave
 // holds.  With eight marks per block, side by side, 28800 unset ones took 6.9
-// us against 4.9, half a million 142 against some 60, and the adjoint of a
+// us against 4.9, half a million 142 against 26, and the adjoint of a
 // 160x192x160 field of up to 8 voxels 971 us against 949.
 template <bool DETMAX, class Items>
 static hipError_t exp_far_(const Items& items, int n_tiles, hipStream_t s) {
