@@ -1719,6 +1719,11 @@ struct HipExecutor : Executor {
   }
   uint64_t held_bytes(JobHandle& h) override { return job_of(h).footprint; }
   void on_device_error() override { ctx->poisoned = true; }
+  // before the plans' host blobs, the jobs' device blocks and their pinned
+  // states (which return to a pool) are given up
+  void drain() noexcept override {
+    if (s) (void)hipStreamSynchronize(s);
+  }
 };
 }  // namespace
 
@@ -1741,10 +1746,9 @@ void Server::loop() {
     return;
   }
   while (sched->wait_for_work()) sched->tick();
-  sched->shutdown();
+  sched->shutdown();  // waits for the stream
   hx->plans.clear();
   hx->sigs.clear();
-  (void)hipStreamSynchronize(hx->s);
   (void)hipStreamDestroy(hx->s);
   hx->s = nullptr;
 }

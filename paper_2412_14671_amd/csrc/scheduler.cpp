@@ -210,6 +210,8 @@ void Scheduler::tick() {
       done_cv_.notify_all();
     }
   } catch (const Error& e) {
+    // the groups stepped before the failure are still in flight
+    ex_.drain();
     std::lock_guard<std::mutex> lk(mu_);
     if (e.st == MUSTER_E_DEVICE) ex_.on_device_error();
     for (auto& t : resident_) finish_ticket(*t, 3, e.st, e.msg);
@@ -220,6 +222,7 @@ void Scheduler::tick() {
 }
 
 void Scheduler::shutdown() {
+  ex_.drain();
   std::lock_guard<std::mutex> lk(mu_);
   stop_ = true;
   for (auto& t : queue_) finish_ticket(*t, 4, MUSTER_E_CANCELLED, "server stopped");

@@ -63,6 +63,10 @@ struct Executor {
   virtual uint64_t held_bytes(JobHandle& h) = 0;
   // A device error ended the tick: every resident job fails with it.
   virtual void on_device_error() = 0;
+  // Waits for everything enqueued, whatever its outcome.  Called before jobs
+  // and groups are released where a failure may have left work in flight (an
+  // executor that enqueues nothing has nothing to wait for).
+  virtual void drain() noexcept {}
 };
 
 struct Ticket {
