@@ -842,6 +842,15 @@ __device__ __forceinline__ bool is_near(const float (&e)[3]) {
   return fmaxf(fabsf(e[0]), fmaxf(fabsf(e[1]), fabsf(e[2]))) < 1.f;
 }
 
+// The same of a voxel whose gradient the adjoint may gather: 0 * g is 0 for a
+// finite g and NaN for any other, which compares as false.  Gathered, a value
+// that is not finite would reach all 27 voxels around (a weight of 0 does not
+// take it out), so its voxel goes to k_exp_far, which takes it to the cell's 8 corners.
+__device__ __forceinline__ bool is_near(const float (&e)[3], const float (&g)[3]) {
+  const float m = fmaxf(fabsf(e[0]), fmaxf(fabsf(e[1]), fabsf(e[2])));
+  return fmaf(0.f, g[0], fmaf(0.f, g[1], fmaf(0.f, g[2], m))) < 1.f;
+}
+
 // ---------------------------------------------------------------------------
 // Exp forward: one squaring u' = u + u o (Omega + u)   (Alg. 1)
 //
@@ -956,11 +965,13 @@ __global__ __launch_bounds__(MT_NT) void k_exp_fwd(const Items items, int n_tile
 // zp adds to the sums of planes zp - 1, zp and zp + 1, which each thread
 // keeps in registers, so a plane's G and displacements are read from LDS
 // once per output column (9 records).  The corners of J_u come from a ring of
-// the last planes of u.  Voxels that are not near take no part here: the
-// block marks their point tile in `far`, and k_exp_far adds what they spread.
+// the last planes of u.  Voxels that are not near, or whose G is not finite,
+// take no part here: the block marks their point tile in `far`, and k_exp_far
+// adds what they spread.
 //
 // Plain sums in a fixed order: no atomics, no fixed point, and the result
-// does not depend on the tiling or on what shares the launch.
+// does not depend on the tiling or on what shares the launch.  Held to 96
+// registers: five blocks per CU (98 would leave four).
 //
 // Bound by vector issue: about 330 instructions per voxel, where the exchange
 // of scatter boxes in LDS that this replaced took 512 and moved 60 bytes per
@@ -971,7 +982,7 @@ __global__ __launch_bounds__(MT_NT) void k_exp_fwd(const Items items, int n_tile
 // with 16 x 16 columns 361, with 16 x 32 300, with 8 x 16 403, with 4 x 64 324.
 // ---------------------------------------------------------------------------
 template <class Items>
-__global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tiles) {
+__global__ __launch_bounds__(MT_NT) GATHER_WAVES void k_exp_bwd(const Items items, int n_tiles) {
   constexpr int PX = MT_PX, ROW = 3 * PX, PLANE = MT_PY * ROW;
   __shared__ float4 ra[2][MT_P1];  // e_z, e_y, e_x, G_z of a plane
   __shared__ float2 rb[2][MT_P1];  // G_y, G_x
@@ -998,22 +1009,24 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tile
 #pragma unroll
     for (int c = 0; c < 3; ++c) g[c] = ldo(gi.c[c], p);
   };
-  // a column's record of plane z; u comes scaled by a
+  // a column's record of plane z, u scaled by a; whether its voxel is gathered
   auto record = [&](int z, const MCol& m, const float (&u)[3], const float (&g)[3]) {
     float e[3];
     hold(u, z, D, m, e);
-    const bool take = m.in && is_near(e);
+    const bool take = m.in && is_near(e, g);
     ra[z & 1][m.place] = make_float4(e[0], e[1], e[2], take ? g[0] : 0.f);
     rb[z & 1][m.place] = make_float2(take ? g[1] : 0.f, take ? g[2] : 0.f);
     float* q = up + (z & 3) * PLANE + (m.place / PX) * ROW + m.place % PX;
 #pragma unroll
     for (int c = 0; c < 3; ++c) q[c * PX] = u[c];
+    return take;
   };
   float nu[3], ng[3], ru[3], rg[3];  // plane zp of the own and the ring column, loaded ahead
   load(tc.z0 - 1, own, nu, ng);
   if (ring) load(tc.z0 - 1, rim, ru, rg);
   float s0[3] = {0.f, 0.f, 0.f}, s1[3] = {0.f, 0.f, 0.f}, s2[3] = {0.f, 0.f, 0.f};
   float pu[3] = {0.f, 0.f, 0.f}, pg[3] = {0.f, 0.f, 0.f};  // own column at plane zp - 1
+  bool near = false;  // the own voxel of plane zp - 1 is gathered
   float res[3];
   for (int zp = tc.z0 - 1;; ++zp) {
     float cu[3], cg[3];
@@ -1025,8 +1038,9 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tile
     // records of plane zp.  The buffers written here were last read two
     // (records) and three (ring of u) planes ago, before the last barrier.
     const bool in_z = zp >= 0 && zp < D && zp <= tc.z1;
+    bool next = false;
     if (in_z) {
-      record(zp, own, cu, cg);
+      next = record(zp, own, cu, cg);
       if (ring) {
         const float v[3] = {a * ru[0], a * ru[1], a * ru[2]};
         record(zp, rim, v, rg);
@@ -1083,7 +1097,7 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tile
       // gradient; clamped axes contribute nothing
       float e[3], jz, jy, jx, v[8], lz, ly_, lx_;
       hold(pu, zo, D, own, e);
-      if (is_near(e)) {
+      if (near) {
         const bool bz = e[0] < 0.f || zo == D - 1, by = e[1] < 0.f || y == H - 1,
                    bx = e[2] < 0.f || x == W - 1;
         const int row = ly + 1 - (by ? 1 : 0), col = lx + 1 - (bx ? 1 : 0);
@@ -1134,11 +1148,23 @@ __global__ __launch_bounds__(MT_NT) void k_exp_bwd(const Items items, int n_tile
       pu[c] = cu[c];
       pg[c] = cg[c];
     }
+    near = next;
   }
 }
 
-// What the voxels that are not near spread, added into the field that
-// k_exp_bwd has written, over the point tiles it marked.  A block looks at
+// v spread over the 8 corners of a cell of one plane by float atomics.
+__device__ __forceinline__ void spread(gfloat* __restrict__ out, int base, int W, int HW,
+                                       const ScatterVox& s, float v) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const float wz = k & 4 ? s.tz : 1.f - s.tz, wy = k & 2 ? s.ty : 1.f - s.ty,
+                wx = k & 1 ? s.tx : 1.f - s.tx;
+    gadd(out + base + (k & 4 ? HW : 0) + (k & 2 ? W : 0) + (k & 1), wz * wy * wx * v);
+  }
+}
+
+// What the voxels that k_exp_bwd left out spread, added into the field that it
+// has written, over the point tiles it marked.  A block looks at
 // `group` marks, a grid apart, with one load and ends there when none is set,
 // which is the usual case: displacements reach a voxel only in the last
 // squarings of a large deformation, and then in neighbouring tiles, which so
@@ -1181,11 +1207,22 @@ __global__ __launch_bounds__(BLOCK) void k_exp_far(const Items items, int n_tile
       float e[3];
       hold(uu[j], vs.z[j], D, m, e);
       sv[j].cz = -1;
-      if (!vs.ok[j] || is_near(e)) continue;
+      float g[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) g[c] = ldo(gin + c * V, vs.p[j]);
+      if (!vs.ok[j] || is_near(e, g)) continue;
       sv[j].cz = cs.az[j].i0; sv[j].cy = cs.ay[j].i0; sv[j].cx = cs.ax[j].i0;
       sv[j].tz = cs.az[j].t; sv[j].ty = cs.ay[j].t; sv[j].tx = cs.ax[j].t;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) sv[j].g[c] = it.oscale * ldo(gin + c * V, vs.p[j]);
+      for (int c = 0; c < 3; ++c) {
+        float v = it.oscale * g[c];
+        if (!(fabsf(v) < INFINITY)) {
+          // no sum of the bins: straight to the corners, in any order
+          if (!DETMAX) spread(gp(it.gout) + c * V, cs.base[j], W, H * W, sv[j], v);
+          v = 0.f;
+        }
+        sv[j].g[c] = v;
+      }
     }
     if (DETMAX) {
       det_bound<BLOCK>(sv, sred, it.js, it.det_slot);
