@@ -1302,25 +1302,21 @@ __global__ __launch_bounds__(CT_Y * CT_X) void k_combine(const Items items, int 
           xm[c] = grad && x > 0 ? ldo(q, p - 1) : 0.f;
           xp[c] = x + 1 < W ? ldo(q, p + 1) : 0.f;
         }
-        // squares summed in float over the components of one voxel, in double
-        // beyond (a conversion per square would be the longest part)
-        float vz = 0.f, vy = 0.f, vx = 0.f;
+        // the differences are floats, their squares and sums doubles
+        auto square = [](double& v, float d) { v = fma((double)d, (double)d, v); };
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           float rg = 0.f;
-          if (z + 1 < D) { const float d = fp[c] - fc[c]; rg -= 2.f * d * inv_mz; vz = fmaf(d, d, vz); }
+          if (z + 1 < D) { const float d = fp[c] - fc[c]; rg -= 2.f * d * inv_mz; square(sz, d); }
           if (z > 0)     { const float d = fc[c] - fm[c]; rg += 2.f * d * inv_mz; }
-          if (y + 1 < H) { const float d = yp[c] - fc[c]; rg -= 2.f * d * inv_my; vy = fmaf(d, d, vy); }
+          if (y + 1 < H) { const float d = yp[c] - fc[c]; rg -= 2.f * d * inv_my; square(sy, d); }
           if (y > 0)     { const float d = fc[c] - ym[c]; rg += 2.f * d * inv_my; }
-          if (x + 1 < W) { const float d = xp[c] - fc[c]; rg -= 2.f * d * inv_mx; vx = fmaf(d, d, vx); }
+          if (x + 1 < W) { const float d = xp[c] - fc[c]; rg -= 2.f * d * inv_mx; square(sx, d); }
           if (x > 0)     { const float d = fc[c] - xm[c]; rg += 2.f * d * inv_mx; }
           g[c] = fmaf(it.reg_w, rg, g[c]);
           fm[c] = fc[c];
           fc[c] = fp[c];
         }
-        sz += (double)vz;
-        sy += (double)vy;
-        sx += (double)vx;
       }
       if (it.ext) {
         // L_L2 and L_ts (Sec. 2.4): linear in the flows of this interval and its neighbours
