@@ -2115,15 +2115,17 @@ __global__ __launch_bounds__(BLOCK) void k_adam(const AdamItem* __restrict__ ite
 // ---------------------------------------------------------------------------
 // SMOOTH_S consecutive outputs of the convolution of a line held in LDS with
 // the taps w: line is the first sample the first output reaches, ls the
-// samples' stride, m the samples read, in multiples of SMOOTH_S.  Every sample
-// feeds each output it reaches (taps outside 0..2r are zero), so an output sums
-// its taps in the order k = 0..2r.
+// samples' stride, m the samples that the eight reach.  Every sample feeds each
+// output (taps outside 0..2r are zero), so an output sums its taps in the order
+// k = 0..2r.  The samples are read in groups of SMOOTH_S and the rest one by one:
+// one beyond the m would make the outputs NaN if it is not finite.
 __device__ __forceinline__ void smooth_chunk(const float* line, int ls, int m,
                                              const float* __restrict__ w,
                                              float (&acc)[SMOOTH_S]) {
 #pragma unroll
   for (int o = 0; o < SMOOTH_S; ++o) acc[o] = 0.f;
-  for (int j = 0; j < m; j += SMOOTH_S) {
+  int j = 0;
+  for (; j + SMOOTH_S <= m; j += SMOOTH_S) {
     float v[SMOOTH_S];
 #pragma unroll
     for (int k = 0; k < SMOOTH_S; ++k) v[k] = line[(j + k) * ls];
@@ -2132,6 +2134,11 @@ __device__ __forceinline__ void smooth_chunk(const float* line, int ls, int m,
     for (int k = 0; k < SMOOTH_S; ++k)
 #pragma unroll
       for (int o = 0; o < SMOOTH_S; ++o) acc[o] = fmaf(t[k - o], v[k], acc[o]);
+  }
+  for (; j < m; ++j) {
+    const float v = line[j * ls];
+#pragma unroll
+    for (int o = 0; o < SMOOTH_S; ++o) acc[o] = fmaf(w[SMOOTH_WPAD + j - o], v, acc[o]);
   }
 }
 
@@ -2166,7 +2173,7 @@ __global__ __launch_bounds__(BLOCK) void k_smooth(const SmoothItem* __restrict__
   const cgfloat* __restrict__ src = gp(it.src) + comp * V;
   gfloat* __restrict__ dst = gp(it.dst) + comp * V;
   const int r = it.radius, L = it.lines, ls = it.lshift;
-  const int m = (2 * r + 2 * SMOOTH_S - 1) / SMOOTH_S * SMOOTH_S;  // samples of a chunk
+  const int m = 2 * r + SMOOTH_S;  // samples of a chunk
   if (it.axis < 2) {
     // lines along z (axis 0) or y (axis 1); the tile is L adjacent x columns
     const int n = it.axis == 0 ? D : H;

@@ -742,8 +742,7 @@ int smooth_item_setup(SmoothItem& it, const int dims[3], int axis, float sigma, 
   const int n = dims[axis];
   const int avail = axis == 2 ? dims[0] * dims[1] : dims[2];
   // staged samples of a line: the outputs' chunks and what they reach beyond
-  const int staged = ceil_div(n, SMOOTH_S) * SMOOTH_S - SMOOTH_S +
-                     ceil_div(2 * r + SMOOTH_S, SMOOTH_S) * SMOOTH_S;
+  const int staged = ceil_div(n, SMOOTH_S) * SMOOTH_S + 2 * r;
   auto need = [&](int L) { return axis == 2 ? L * (staged | 1) : staged * L; };
   int L = 64;
   while (L > 1 && (L / 2 >= avail || need(L) > (axis == 2 ? SMOOTH_LDS_ROWS : SMOOTH_LDS_COLS)))
