@@ -316,8 +316,9 @@ muster_status muster_exp(muster_ctx* ctx, void* stream, const int dims[3], int K
                          const float* svf_dev, float* disp_dev, float* steps_dev);
 /* grad_svf = d<G, Exp(sign*svf)>/dsvf for G = grad_disp (adjoint of
  * muster_exp), in MUSTER_EXP_STORE or _RECOMPUTE mode, with the same kernels
- * as the registration's backward pass.  mode | MUSTER_EXP_FLAT is accepted
- * and means the same: every step exchanges plain fields. */
+ * as the registration's backward pass.  mode | MUSTER_EXP_FLAT gives the same
+ * values; in recompute mode it keeps two squaring steps instead of four, five
+ * fields of scratch in all. */
 #define MUSTER_EXP_FLAT 4
 muster_status muster_exp_bwd(muster_ctx* ctx, void* stream, const int dims[3], int K,
                              int sign, const float* svf_dev, const float* grad_disp_dev,

@@ -112,8 +112,8 @@ class Context:
         return (out, st) if steps else out
 
     def exp_bwd(self, svf, grad_disp, K, sign=1, mode="store", flat=False):
-        """Adjoint of exp, with the registration's kernels.  flat is accepted and
-        changes nothing: every squaring step exchanges plain fields."""
+        """Adjoint of exp, with the registration's kernels.  flat changes no value:
+        in recompute mode two squaring steps are kept instead of four."""
         out = torch.empty_like(svf)
         m = {"store": L.EXP_STORE, "recompute": L.EXP_RECOMPUTE}[mode]
         if flat:

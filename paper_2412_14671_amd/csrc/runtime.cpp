@@ -187,7 +187,7 @@ static int per_dir_fields(const muster_params& p) {
 // Fields per direction that a job holds: u_K and, in recompute mode, a ring of
 // the last REC_SLOTS steps before it (two more than the footprint names; they
 // fit the room it holds for the adjoint).
-static int ring_slots(int K) { return std::max(1, std::min(REC_SLOTS, K - 1)); }
+static int ring_slots(int K, int most = REC_SLOTS) { return std::max(1, std::min(most, K - 1)); }
 static int held_fields(const muster_params& p) {
   return p.exp_mode == MUSTER_EXP_STORE ? p.K : 1 + ring_slots(p.K);
 }
@@ -195,8 +195,8 @@ static int held_fields(const muster_params& p) {
 // Recompute mode: whether u_1..u_s are formed anew before the adjoint's step s.
 // The ring then holds the last steps up to s, so that happens once per turn of
 // the ring, and not before the first, whose steps the forward pass has left.
-static bool ring_refill(int K, int s) {
-  return s >= 1 && s < K - 1 && (K - 1 - s) % ring_slots(K) == 0;
+static bool ring_refill(int K, int s, int slots) {
+  return s >= 1 && s < K - 1 && (K - 1 - s) % slots == 0;
 }
 
 uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
@@ -832,7 +832,8 @@ void add_exp_fwd_step(Builder& b, const std::vector<Job*>& jobs, int s, bool rec
   double bytes = 0;
   for (Job* J : jobs) {
     if (s >= J->K()) continue;
-    if (recompute_only && (J->p.exp_mode != MUSTER_EXP_RECOMPUTE || !ring_refill(J->K(), upto)))
+    if (recompute_only && (J->p.exp_mode != MUSTER_EXP_RECOMPUTE ||
+                           !ring_refill(J->K(), upto, ring_slots(J->K()))))
       continue;
     const int* d = J->ldims[J->level];
     const float scale = std::ldexp(1.f, -J->K());
@@ -2287,13 +2288,16 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     check_dims(dims, 2);
     NEED(K >= 1 && K <= 20, "K must be in 1..20");
     NEED(sign == 1 || sign == -1, "sign must be +1 or -1");
+    // MUSTER_EXP_FLAT keeps two squaring steps, so that the call fits the five
+    // fields of scratch that it always took
+    const int ring = ring_slots(K, (mode & MUSTER_EXP_FLAT) ? 2 : REC_SLOTS);
     mode &= ~MUSTER_EXP_FLAT;
     NEED(mode == MUSTER_EXP_STORE || mode == MUSTER_EXP_RECOMPUTE, "bad mode");
     std::lock_guard<std::mutex> lk(ctx->mu);
     hipStream_t hs = (hipStream_t)stream;
     const size_t V = (size_t)dims[0] * dims[1] * dims[2];
     const size_t F = 3 * V;
-    const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 1) : ring_slots(K);
+    const int nstore = mode == MUSTER_EXP_STORE ? std::max(K - 1, 1) : ring;
     const int ntp = point_tiles(dims[0], dims[1], dims[2]);
     // the last step writes grad_svf unless it still reads what lies there
     const bool direct =
@@ -2323,7 +2327,7 @@ muster_status muster_exp_bwd(muster_ctx* h, void* stream, const int dims[3], int
     };
     advance(K - 1);
     for (int s = K - 1; s >= 0; --s) {
-      if (mode == MUSTER_EXP_RECOMPUTE && ring_refill(K, s)) advance(s);
+      if (mode == MUSTER_EXP_RECOMPUTE && ring_refill(K, s, ring)) advance(s);
       const float* us_src = s == 0 ? svf : ustep(s);
       std::vector<ExpBwdItem> one(1);
       ExpBwdItem& it = one[0];
