@@ -219,17 +219,14 @@ uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
   // deterministic mode: 64-bit fixed-point twins of the consecutive-field
   // gradients and of the Exp-backward ping-pong
   if (p.deterministic) bytes += 6 * n1 * 3 * V * sizeof(long long);
-  {
+  if (p.K >= 2) {
+    // Room for the Exp adjoint, per direction: 24 KB for each of two steps
+    // and point tile.  The figure servers have sized their budgets by; the
+    // adjoint's dense exchange takes less of it (its marks).  One squaring
+    // counts none: its marks lie in a ping-pong field.
     const uint64_t tiles = (uint64_t)point_tiles(fd[0], fd[1], fd[2]);
-    if (p.K >= 2) {
-      // Room for the Exp adjoint, per direction: 24 KB for each of two steps
-      // and point tile.  The figure servers have sized their budgets by; the
-      // adjoint's dense exchange takes less of it (its marks).
-      bytes += 2 * 2 * n1 * tiles * (3 * SCATTER_CELLS * sizeof(float) + 8 * sizeof(int));
-      bytes += 2 * n1 * p.K * sizeof(int) + 2 * 256;
-    } else {
-      bytes += 2 * n1 * tiles * sizeof(int);
-    }
+    bytes += 2 * 2 * n1 * tiles * (3 * SCATTER_CELLS * sizeof(float) + 8 * sizeof(int));
+    bytes += 2 * n1 * p.K * sizeof(int) + 2 * 256;
   }
   uint64_t imgs = 0;
   for (int l = 0; l < p.levels - 1; ++l) {
@@ -386,7 +383,7 @@ std::unique_ptr<Job> make_job(Ctx* ctx, const muster_job& jd) {
     MUSTER_HIP(launch_fill(J.m_det64.as<float>(), (int64_t)(12 * n1 * 3 * V0), 0.f, nullptr));
     MUSTER_HIP(hipStreamSynchronize(nullptr));
   }
-  J.m_far.alloc(ctx, 2 * n1 * (size_t)J.tiles_fine * sizeof(int));
+  if (J.p.K >= 2) J.m_far.alloc(ctx, 2 * n1 * (size_t)J.tiles_fine * sizeof(int));
   size_t img = 0;
   for (int l = 0; l < L - 1; ++l) img += (size_t)N * J.VI(l);
   J.m_img.alloc(ctx, std::max<size_t>(img, 1) * sizeof(float));
@@ -525,7 +522,11 @@ void job_begin_level(Job& J, int level, hipStream_t s) {
   }
   if (J.p.rigid) rigid_begin_level(J, level, s);
   // the marks are ints; 0.0f has the same bits as 0
-  MUSTER_HIP(launch_fill((float*)J.m_far.p, (int64_t)(2 * n1 * J.tiles_fine), 0.f, s));
+  if (J.p.K >= 2)
+    MUSTER_HIP(launch_fill((float*)J.m_far.p, (int64_t)(2 * n1 * J.tiles_fine), 0.f, s));
+  else
+    for (size_t i = 0; i < n1; ++i)
+      MUSTER_HIP(launch_fill((float*)J.far(2 * (int)i), 2 * (int64_t)J.tiles(level), 0.f, s));
   JobState st{};
   const int prev_nonfinite = level > 0 ? J.host_state->nonfinite : 0;
   st.t = 0;

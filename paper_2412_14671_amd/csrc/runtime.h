@@ -188,7 +188,7 @@ struct Job {
   DevMem m_pimg, m_gimg;             // pair fields and their gradients on the image grid (ff > 1)
   DevMem m_rigid;                    // RigidState of sessions 1..N-1 (params.rigid)
   float* rigid_out = nullptr;
-  DevMem m_far;                      // Exp backward: marks of k_exp_far per direction and point tile
+  DevMem m_far;                      // marks of k_exp_far per direction and point tile (K >= 2)
   DevMem m_det64, m_flags;           // deterministic mode: fixed-point twins (see det64_*), flags
   float* phi = nullptr;              // may alias the caller's field in grad_mode
   float* mbuf = nullptr;
@@ -228,7 +228,14 @@ struct Job {
     return smoothing() || p.K >= 2 ? field(m_t1.as<float>(), (size_t)i) : pp(2 * i, 1);
   }
   int tiles_fine = 0;                // point tiles of the finest grid
-  int* far(int dir) const { return m_far.as<int>() + (size_t)dir * tiles_fine; }
+  int tiles(int l) const { return point_tiles(ldims[l][0], ldims[l][1], ldims[l][2]); }
+  // marks of k_exp_far (K = 1: both directions' in the one ping-pong field of
+  // the interval that nothing else uses; a field has three floats per voxel, a
+  // tile at least one voxel)
+  int* far(int dir) const {
+    if (p.K >= 2) return m_far.as<int>() + (size_t)dir * tiles_fine;
+    return reinterpret_cast<int*>(pp(dir | 1, 1)) + (size_t)(dir & 1) * tiles(level);
+  }
   int* flag(int dir, int s) const { return m_flags.as<int>() + (size_t)dir * p.K + s; }
   bool det() const { return p.deterministic != 0; }
   // 64-bit fixed-point twins of the gradient of consecutive field dir (the
