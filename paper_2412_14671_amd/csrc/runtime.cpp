@@ -246,33 +246,27 @@ uint64_t job_footprint(int N, const int dims[3], const muster_params& p) {
 JobState* Ctx::take_host_state() {
   {
     std::lock_guard<std::mutex> lk(host_mu);
-    if (!host_states.empty()) {
-      JobState* h = host_states.back();
-      host_states.pop_back();
-      return h;
-    }
+    if (n_host_states > 0) return host_states[--n_host_states];
   }
   JobState* h = nullptr;
   MUSTER_HIP(hipHostMalloc((void**)&h, sizeof(JobState), hipHostMallocDefault));
   return h;
 }
 
-void Ctx::give_host_state(JobState* h) {
+void Ctx::give_host_state(JobState* h) noexcept {
   {
     std::lock_guard<std::mutex> lk(host_mu);
-    if (host_states.size() < MAX_HOST_STATES) {
-      host_states.reserve(MAX_HOST_STATES);
-      host_states.push_back(h);
+    if (n_host_states < MAX_HOST_STATES) {
+      host_states[n_host_states++] = h;
       return;
     }
   }
   (void)hipHostFree(h);
 }
 
-void Ctx::free_host_states() {
+void Ctx::free_host_states() noexcept {
   std::lock_guard<std::mutex> lk(host_mu);
-  for (JobState* h : host_states) (void)hipHostFree(h);
-  host_states.clear();
+  while (n_host_states > 0) (void)hipHostFree(host_states[--n_host_states]);
 }
 
 Job::~Job() {

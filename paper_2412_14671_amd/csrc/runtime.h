@@ -98,12 +98,13 @@ struct Ctx {
   std::mutex mu;                     // serialises API calls that use ws
   // Pinned job states kept for the next job (allocating and freeing one costs
   // 95 us), at most MAX_HOST_STATES; given back by trim and with the context.
-  static constexpr size_t MAX_HOST_STATES = 64;
-  std::vector<JobState*> host_states;
+  static constexpr int MAX_HOST_STATES = 64;
+  JobState* host_states[MAX_HOST_STATES];
+  int n_host_states = 0;
   std::mutex host_mu;
   JobState* take_host_state();
-  void give_host_state(JobState* h);
-  void free_host_states();
+  void give_host_state(JobState* h) noexcept;   // from destructors: allocates nothing
+  void free_host_states() noexcept;
   void* step_items = nullptr;        // device buffer for single-step item tables
   size_t step_items_bytes = 0;
   double* step_acc = nullptr;        // device doubles for single-step results
