@@ -194,7 +194,8 @@ muster_status muster_ctx_destroy(muster_ctx* ctx);
  *                         that shape, then cached in the context (and, when
  *                         the environment variable MUSTER_TUNE_CACHE names a
  *                         file, appended to it and read back by later
- *                         contexts);
+ *                         contexts; lines of another form, such as those of
+ *                         builds that timed other cuts, are passed over);
  *   MUSTER_TILES_FIXED    the given shape and zchunk.
  * zchunk is capped at D.  Results do not depend on the tiling beyond float
  * rounding.  MUSTER_E_INVALID for an unknown mode, shape or zchunk < 1. */

@@ -1753,11 +1753,17 @@ void Server::loop() {
 // Autotuner of the window-statistics tiling.  Each candidate (tile shape,
 // z chunk) runs the statistics and gradient kernels on a scratch problem of
 // the same shape (two patterned images and a patterned pair field), one
-// untimed and three timed repetitions; the fastest median wins.  Results are
-// kept per context and, with MUSTER_TUNE_CACHE set, appended to that file and
-// read back by later contexts.
+// untimed and three timed repetitions, cut along z as a launch of as many pairs
+// is (set_sim_parts); the fastest median wins.  Results are kept per context and,
+// with MUSTER_TUNE_CACHE set, appended to that file and read back by later
+// contexts.
 // ---------------------------------------------------------------------------
 namespace {
+
+// An entry of the cache file.  The word says what was timed (launches cut in
+// parts); lines that begin otherwise, such as those of seven numbers that timed
+// whole chunks, are passed over.
+#define TUNE_ENTRY "parts %d %d %d %d %d %d %d"
 
 std::vector<int> tune_key(const int d[3], int window, int metric) {
   return {d[0], d[1], d[2], window, metric};
@@ -1767,7 +1773,7 @@ void save_tune_entry(Ctx* ctx, const std::vector<int>& k, const SimTile& t) {
   if (ctx->tune_path.empty()) return;
   FILE* f = std::fopen(ctx->tune_path.c_str(), "a");
   if (!f) return;
-  std::fprintf(f, "%d %d %d %d %d %d %d\n", k[0], k[1], k[2], k[3], k[4], t.shape, t.zc);
+  std::fprintf(f, TUNE_ENTRY "\n", k[0], k[1], k[2], k[3], k[4], t.shape, t.zc);
   std::fclose(f);
 }
 
@@ -1801,7 +1807,7 @@ SimTile tune_sim_tile(Ctx* ctx, const int dims[3], int window, int metric, hipSt
   img.alloc(ctx, 2 * V * sizeof(float));
   fld.alloc(ctx, (size_t)P * per_pair);
   acc.alloc(ctx, sizeof(double));
-  item.alloc(ctx, (size_t)P * sizeof(SimItem));
+  item.alloc(ctx, 2 * (size_t)P * sizeof(SimItem));  // statistics, gradient
   MUSTER_HIP(launch_pattern(img.as<float>(), (int64_t)(2 * V), dims, 0.5f, 0.4f, 0.3f, s));
   MUSTER_HIP(launch_pattern(fld.as<float>(), (int64_t)(9 * V * P), dims, 0.f, 1.5f, 1.1f, s));
   const int r = (window - 1) / 2;
@@ -1838,17 +1844,25 @@ SimTile tune_sim_tile(Ctx* ctx, const int dims[3], int window, int metric, hipSt
   float best_ms = 1e30f;
   for (int shape = 0; shape < SIM_SHAPES; ++shape)
     for (int zc : zcs) {
-      const int per = stat_tiles(dims[0], dims[1], dims[2], zc, zc, shape);
+      // what is timed is what a launch of these pairs takes
+      for (SimItem& it : its) it.zc = zc;
+      set_sim_parts(its, window, shape);
+      const int zs = its[0].zs, zg = its[0].zg;
+      const int st = stat_tiles(dims[0], dims[1], dims[2], zc, zs, shape),
+                gt = grad_tiles(dims[0], dims[1], dims[2], zg, shape);
+      std::vector<SimItem> both(its);
+      both.insert(both.end(), its.begin(), its.end());
       for (int k = 0; k < P; ++k) {
-        its[k].zc = its[k].zs = its[k].zg = zc;  // what is timed is this cut
-        its[k].tile0 = k * per;
+        both[k].tile0 = k * st;
+        both[P + k].tile0 = k * gt;
       }
-      MUSTER_HIP(hipMemcpyAsync(item.p, its.data(), (size_t)P * sizeof(SimItem),
+      MUSTER_HIP(hipMemcpyAsync(item.p, both.data(), 2 * (size_t)P * sizeof(SimItem),
                                 hipMemcpyHostToDevice, s));
+      MUSTER_HIP(hipStreamSynchronize(s));
       const SimItem* d_it = item.as<SimItem>();
       auto once = [&] {
-        MUSTER_HIP(launch_sim_stats(d_it, P, P * per, window, metric, shape, s));
-        MUSTER_HIP(launch_sim_grad(d_it, P, P * per, window, shape, s));
+        MUSTER_HIP(launch_sim_stats(d_it, P, P * st, window, metric, shape, s));
+        MUSTER_HIP(launch_sim_grad(d_it + P, P, P * gt, window, shape, s));
       };
       once();
       float t[3];
@@ -1861,8 +1875,10 @@ SimTile tune_sim_tile(Ctx* ctx, const int dims[3], int window, int metric, hipSt
       }
       std::sort(t, t + 3);
       if (std::getenv("MUSTER_TUNE_VERBOSE"))
-        std::fprintf(stderr, "muster tune %dx%dx%d w%d m%d (%d pairs): shape %d zchunk %d  %.4f ms\n",
-                     dims[0], dims[1], dims[2], window, metric, P, shape, zc, (double)t[1]);
+        std::fprintf(stderr,
+                     "muster tune %dx%dx%d w%d m%d (%d pairs): shape %d zchunk %d parts %d "
+                     "gradient %d  %.4f ms\n",
+                     dims[0], dims[1], dims[2], window, metric, P, shape, zc, zs, zg, (double)t[1]);
       if (t[1] < best_ms) {
         best_ms = t[1];
         best.shape = shape;
@@ -1882,8 +1898,11 @@ void load_tune_cache(Ctx* ctx) {
   FILE* f = std::fopen(path, "r");
   if (!f) return;
   int D, H, W, w, m, sh, zc;
-  while (std::fscanf(f, "%d %d %d %d %d %d %d", &D, &H, &W, &w, &m, &sh, &zc) == 7)
-    if (sh >= 0 && sh < SIM_SHAPES && zc >= 1 && zc <= D) ctx->tuned[{D, H, W, w, m}] = SimTile{sh, zc};
+  char line[256];
+  while (std::fgets(line, sizeof line, f))
+    if (std::sscanf(line, TUNE_ENTRY, &D, &H, &W, &w, &m, &sh, &zc) == 7 && sh >= 0 &&
+        sh < SIM_SHAPES && zc >= 1 && zc <= D)
+      ctx->tuned[{D, H, W, w, m}] = SimTile{sh, zc};
   std::fclose(f);
 }
 
