@@ -84,8 +84,10 @@ typedef struct muster_params {
                                       squaring fields for the backward pass, or
                                       the last one and a ring of up to four others,
                                       formed anew from phi as the pass goes back  */
-  int use_graph;                   /* 1: replay each level's iteration as a
-                                      captured hipGraph; 0: eager launches        */
+  int use_graph;                   /* 1: replay the iteration of each level of
+                                      four steps or more as a captured hipGraph
+                                      (shorter levels are launched: the same
+                                      work); 0: eager launches                    */
   float smooth_sigma;              /* Gaussian smoothing of the flow before Exp
                                       (Sec. 2.4, Appendix A): the transfer
                                       function exp(-sigma^2 |omega|^2 / 2) on the
@@ -260,9 +262,9 @@ muster_status muster_register(muster_ctx* ctx, void* stream, int N, const int di
 
 /* Batched registration of n_jobs subjects with uneven N and grids: every
  * stage of one iteration runs as one launch over all jobs, and the iteration
- * is replayed from one captured hipGraph per level.  All jobs must share
- * levels, iters, K, window and metric; reports[n_jobs] receives per-job
- * results.  Each job's result matches muster_register on it alone. */
+ * is replayed from one captured hipGraph per level (see use_graph).  All jobs
+ * must share levels, iters, K, window and metric; reports[n_jobs] receives
+ * per-job results.  Each job's result matches muster_register on it alone. */
 muster_status muster_register_batch(muster_ctx* ctx, void* stream, int n_jobs,
                                     const muster_job* jobs, muster_report* reports);
 

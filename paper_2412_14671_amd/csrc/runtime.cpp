@@ -1571,6 +1571,9 @@ void Plan::replay(hipStream_t s) { MUSTER_HIP(hipGraphLaunch(exec, s)); }
 // ---------------------------------------------------------------------------
 // batched registration engine (one or many jobs in lockstep)
 // ---------------------------------------------------------------------------
+// Shortest level whose iteration is captured (muster.h states it).
+constexpr int GRAPH_MIN_STEPS = 4;
+
 static void run_level(Ctx* ctx, std::vector<Job*>& jobs, int level, hipStream_t s, bool use_graph) {
   const int T = jobs[0]->p.iters[level];
   Range range("muster level %d: %zu jobs, %d steps, %dx%dx%d", level, jobs.size(), T,
@@ -1583,9 +1586,13 @@ static void run_level(Ctx* ctx, std::vector<Job*>& jobs, int level, hipStream_t 
   plan->upload(ctx, s);
   MUSTER_HIP(hipStreamSynchronize(s));
   const double t0 = now_seconds();
-  // capturing and instantiating an iteration costs the host about what
-  // launching it three times does
-  if (use_graph && !ctx->timing && T >= 4) {
+  // Capturing and instantiating an iteration takes 60 to 90 us for one job and
+  // 180 us for eight (by levels of 1 to 10 steps with and without it), and a
+  // replayed step takes the device's time, as a launched one does (three sessions
+  // of 32^3: 160 us either way).  What a replay saves is the host's launches, which
+  // few steps do not earn back: three sessions of 32^3, two steps, 588 us captured
+  // and 528 launched.
+  if (use_graph && !ctx->timing && T >= GRAPH_MIN_STEPS) {
     plan->capture(ctx, s);
     for (int t = 0; t < T; ++t) plan->replay(s);
   } else {
