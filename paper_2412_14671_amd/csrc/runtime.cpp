@@ -613,8 +613,7 @@ void job_final_outputs(Job& J, hipStream_t s) {
     MUSTER_HIP(hipMemcpyAsync(J.rigid_out, out.data(), out.size() * sizeof(float),
                               hipMemcpyHostToDevice, s));
   }
-  MUSTER_HIP(hipStreamSynchronize(s));
-  flight.done();
+  flight.wait();
 }
 
 // ---------------------------------------------------------------------------
@@ -1581,7 +1580,10 @@ static void run_level(Ctx* ctx, std::vector<Job*>& jobs, int level, hipStream_t 
   std::unique_ptr<Plan> plan;
   StreamGuard flight(s);
   for (Job* J : jobs) job_begin_level(*J, level, s);
-  if (T <= 0) return;
+  if (T <= 0) {
+    flight.wait();
+    return;
+  }
   plan = build_plan(jobs, PLAN_ITERATION);
   plan->upload(ctx, s);
   MUSTER_HIP(hipStreamSynchronize(s));
@@ -1604,8 +1606,7 @@ static void run_level(Ctx* ctx, std::vector<Job*>& jobs, int level, hipStream_t 
   if (ctx->timing) resolve_timing(ctx);
   for (Job* J : jobs)
     MUSTER_HIP(hipMemcpyAsync(J->host_state, J->js, sizeof(JobState), hipMemcpyDeviceToHost, s));
-  MUSTER_HIP(hipStreamSynchronize(s));
-  flight.done();
+  flight.wait();
 }
 
 static void fill_report(Job& J, double t0, muster_report* rep, hipStream_t s) {
@@ -1677,6 +1678,7 @@ struct HipExecutor : Executor {
     h->job = make_job(ctx, j);
     StreamGuard flight(s);
     job_begin_level(*h->job, 0, s);
+    flight.wait();
     return h;
   }
   void step(const GroupKey& key, const std::vector<JobHandle*>& group,
@@ -1714,6 +1716,7 @@ struct HipExecutor : Executor {
   void begin_level(JobHandle& h, int level) override {
     StreamGuard flight(s);
     job_begin_level(job_of(h), level, s);
+    flight.wait();
   }
   void finish(JobHandle& h, double t_submit, muster_report* rep) override {
     job_final_outputs(job_of(h), s);
@@ -2248,8 +2251,7 @@ muster_status muster_loss_backward(muster_ctx* h, void* stream, muster_saved* sa
     StreamGuard flight(s);
     plan->upload(ctx, s);
     plan->run(ctx, s);
-    MUSTER_HIP(hipStreamSynchronize(s));
-    flight.done();
+    flight.wait();
     if (ctx->timing) resolve_timing(ctx);
     saved->used = true;
   });

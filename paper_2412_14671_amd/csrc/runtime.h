@@ -120,8 +120,10 @@ struct Ctx {
   Ctx(uint64_t budget, int device) : arena(budget, device) {}
 };
 
-// Waits for the stream when a scope is left before done(): work in flight must
-// not outlive the memory that the scope's owners give back.
+// Waits for the stream when a scope is left before done() or wait(), by an
+// error: work in flight must not outlive the memory that the scope's owners give
+// back.  A scope that ends well calls one of them, so that what a wait reports
+// is not lost.
 struct StreamGuard {
   hipStream_t s;
   bool armed = true;
@@ -132,6 +134,10 @@ struct StreamGuard {
     if (armed) (void)hipStreamSynchronize(s);
   }
   void done() { armed = false; }
+  void wait() {
+    armed = false;
+    MUSTER_HIP(hipStreamSynchronize(s));
+  }
 };
 
 // Device allocation owned through the context's arena.
