@@ -83,7 +83,9 @@ typedef struct muster_params {
   int exp_mode;                    /* MUSTER_EXP_STORE or _RECOMPUTE: keep the K
                                       squaring fields for the backward pass, or
                                       the last one and a ring of up to four others,
-                                      formed anew from phi as the pass goes back  */
+                                      formed anew from phi as the pass goes back
+                                      (up to K 5 the ring holds every step: the
+                                      memory and the work of _STORE)              */
   int use_graph;                   /* 1: replay the iteration of each level of
                                       four steps or more as a captured hipGraph
                                       (shorter levels are launched: the same
@@ -240,8 +242,11 @@ const char* muster_version(void);
  * (0.9, 0.999, 1e-8), store mode, graphs on, no smoothing. */
 muster_status muster_params_default(muster_params* p);
 
-/* Device bytes a job of N sessions on grid dims needs under params
- * (workspaces only; the caller's images and outputs are not counted). */
+/* Device bytes to plan for a job of N sessions on grid dims under params
+ * (workspaces only; the caller's images and outputs are not counted): the
+ * figure the server admits by.  An upper bound: for K >= 2 it counts 48 KB per
+ * direction and 8x8x16 voxels for the Exp adjoint, most of which the job does
+ * not allocate.  What a job held is its report's footprint_bytes. */
 muster_status muster_footprint(int N, const int dims[3], const muster_params* p,
                                uint64_t* bytes);
 
@@ -411,7 +416,10 @@ enum {
   MUSTER_K_EXP_FWD = 0, MUSTER_K_COMPOSE_FWD, MUSTER_K_SIM_STATS, MUSTER_K_SIM_GRAD,
   MUSTER_K_COMPOSE_BWD, MUSTER_K_EXP_BWD, MUSTER_K_ADAM, MUSTER_K_FINISH,
   MUSTER_K_POOL, MUSTER_K_UPSAMPLE, MUSTER_K_SMOOTH, MUSTER_K_UPSAMPLE_ADJ, MUSTER_K_RIGID,
-  MUSTER_K_WARP, MUSTER_K_UNSTAGE, MUSTER_K_COUNT
+  MUSTER_K_WARP,
+  MUSTER_K_UNSTAGE,   /* "unstage": the combination of the SVF gradients with the
+                         regularisers, and the Exp adjoint's pass over far voxels */
+  MUSTER_K_COUNT
 };
 /* When enabled, eager launches (graphs off) of each kernel class are
  * bracketed by HIP events on the stream they run on. */

@@ -120,14 +120,11 @@ __device__ __forceinline__ Ax axis_pos(float q, int n) {
 
 __device__ __forceinline__ float lerp_(float a, float b, float t) { return fmaf(t, b - a, a); }
 
-// Two consecutive floats in one 8-byte load (dword alignment suffices for
-// multi-dword global loads); halves the address work of a gather.
-__device__ __forceinline__ float2a ld2(const cgfloat* p) { return *(const GLOBAL float2a*)p; }
-
 // Loads at element i of a plane whose base is uniform across the wave: the
 // byte offset is formed in 32 bits (i < 2^30 for any volume the library
 // accepts), so the load takes the scalar base plus a 32-bit vector offset
-// instead of a 64-bit vector address.
+// instead of a 64-bit vector address.  ld2o takes two consecutive floats in one
+// 8-byte load (dword alignment suffices for multi-dword global loads).
 __device__ __forceinline__ float2a ld2o(const cgfloat* plane, uint32_t i) {
   return *(const GLOBAL float2a*)((const GLOBAL char*)plane + (i << 2));
 }
@@ -344,29 +341,6 @@ __device__ __forceinline__ void sample_cells(const cgfloat* __restrict__ f, int 
     for (int j = 0; j < VPT; ++j) load8(f + c * V, cs.base[j], W, HW, v[j]);
 #pragma unroll
     for (int j = 0; j < VPT; ++j) out[j][c] = tri_val(v[j], cs.az[j].t, cs.ay[j].t, cs.ax[j].t);
-  }
-}
-
-// (J^T g) at the cells, J the Jacobian of a * f (rows: components of f,
-// columns: z, y, x; clamped axes contribute nothing).
-__device__ __forceinline__ void jt_cells(const cgfloat* __restrict__ f, float a, int V, int H,
-                                         int W, const CellSet& cs, const float (&g)[VPT][3],
-                                         float (&acc)[VPT][3]) {
-  const int HW = H * W;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    float v[VPT][8];
-#pragma unroll
-    for (int j = 0; j < VPT; ++j) load8(f + c * V, cs.base[j], W, HW, v[j]);
-#pragma unroll
-    for (int j = 0; j < VPT; ++j) {
-      float dz, dy, dx;
-      tri_grad(v[j], cs.az[j].t, cs.ay[j].t, cs.ax[j].t, dz, dy, dx);
-      const float gc = a * g[j][c];
-      acc[j][0] = fmaf(dz * cs.az[j].live, gc, acc[j][0]);
-      acc[j][1] = fmaf(dy * cs.ay[j].live, gc, acc[j][1]);
-      acc[j][2] = fmaf(dx * cs.ax[j].live, gc, acc[j][2]);
-    }
   }
 }
 
@@ -862,6 +836,12 @@ __device__ __forceinline__ bool is_near(const float (&e)[3], const float (&g)[3]
 // cache.  Against a box of sampled cells found and loaded per 8 x 8 x 16 tile
 // (187 vector instructions per voxel, about 100 here): one 160x192x160 field
 // 34.0 -> 28.3 us, six of them at once 38.7 -> 29.8 us per field.
+//
+// Far voxels lack the reuse that the box gave.  A whole integration of that
+// field at K 7, before and now: 248 -> 207 us at 2.5 voxels, 239 -> 221 at 8, but
+// 247 -> 261 at 16 and 293 -> 354 at 40, where most squarings are far.  A box for
+// blocks of far voxels inside this kernel wins less than half of that back and
+// costs near fields 2 %.
 // ---------------------------------------------------------------------------
 template <class Items>
 __global__ __launch_bounds__(MT_NT) void k_exp_fwd(const Items items, int n_tiles) {
@@ -1664,8 +1644,9 @@ __global__ __launch_bounds__(BLOCK) void k_warp(const Items items, int n_tiles) 
 // of a chunk: parts are multiples of w windows, so each starts where the sums
 // are formed anew and the same values come out however the chunk is cut.
 //
-// Bound by vector issue and by the barriers of a slice.  The places of a
-// thread's segments are worked out once, waves without a second patch column
+// Bound by vector issue and by the four barriers of a slice (z-sums written,
+// x-sums written, finished sums written, finished sums read: sharing the z-sums'
+// LDS costs the last).  The places of a thread's segments are worked out once, waves without a second patch column
 // skip it, and the finished sums take the z-sums' LDS: three blocks of 16 x 32
 // columns share a CU.  12 pairs of 160x192x160 at w 7: 600 -> 417 us.
 template <int R, int TY, int TX>
@@ -1690,7 +1671,7 @@ __global__ __launch_bounds__(TY * TX) void k_sim_stats(const Items items, int n_
   __shared__ double red[NT / 64];
   const int tile = xcd_remap(blockIdx.x, n_tiles);
   const SimItem it = items.at(tile);
-  const int D = it.D, H = it.H, W = it.W, HW = H * W, V = D * HW;
+  const int D = it.D, H = it.H, W = it.W, HW = H * W;
   // the block's columns, its chunk [c0, c1) and its part [z0, z1) of it
   const STile tc = stat_tile<TY, TX>(tile - it.tile0, D, H, W, 1);
   const int parts = (it.zc + it.zs - 1) / it.zs;
@@ -2524,7 +2505,7 @@ static hipError_t compose_fwd_(const Items& items, int n_tiles, hipStream_t s) {
 }
 
 // Marks per block of k_exp_far: a launch is about as many blocks as walk at
-// once (100 VGPRs: four per CU), up to the 64 marks that one load of a wave
+// once (97 to 110 VGPRs: four per CU), up to the 64 marks that one load of a wave
 // holds.  With eight marks per block, side by side, 28800 unset ones took 6.9
 // us against 4.9, half a million 142 against 26, and the adjoint of a
 // 160x192x160 field of up to 8 voxels 971 us against 949.
